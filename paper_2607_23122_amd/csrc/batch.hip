@@ -75,6 +75,7 @@ __device__ inline void tile_pixel(int packing, int tw, int th, int it, int lane,
 // in (tile_w * tile_h / 64) passes of one ray per lane.  Bounded to 7 waves
 // per SIMD: with both effects' walks inlined it takes 82 registers (5 waves)
 // otherwise, measured 4% slower.
+template <bool FAR>
 __global__ __launch_bounds__(kBBlock, 7) void batch_trace_kernel(const BatchView *__restrict__ views,
                                                               const uint32_t *__restrict__ t_first,
                                                               const uint32_t *__restrict__ t_tiles_x, int nviews,
@@ -108,7 +109,7 @@ __global__ __launch_bounds__(kBBlock, 7) void batch_trace_kernel(const BatchView
             const int px = tx * tw + lx, py = ty * th + ly;
             // every lane calls (the view's mode is the wave's)
             if (V.mode == OCR_AO)
-                trace_pixel<OCR_AO>(V.bvh, V.g, V.R, V.L, V.sd, V.sample, V.occ, px, py, px < w && py < h,
+                trace_pixel<OCR_AO, false, LightF, FAR>(V.bvh, V.g, V.R, V.L, V.sd, V.sample, V.occ, px, py, px < w && py < h,
                                     stack + threadIdx.x, kBBlock, wstack[threadIdx.x >> 6]);
             else
                 trace_pixel<OCR_SHADOW>(V.bvh, V.g, V.R, V.L, V.sd, V.sample, V.occ, px, py, px < w && py < h,
@@ -216,9 +217,10 @@ hipError_t launch_batch_reset(uint32_t *ctr, hipStream_t st) {
 }
 
 hipError_t launch_batch_trace(const BatchView *views, const uint32_t *t_first, const uint32_t *t_tiles_x, int nviews,
-                              const uint32_t *q_start, uint32_t *ctr, int tile_w, int tile_h, int packing, int grid,
-                              hipStream_t st) {
-    hipLaunchKernelGGL(batch_trace_kernel, dim3(grid), dim3(kBBlock), 0, st, views, t_first, t_tiles_x, nviews,
+                              const uint32_t *q_start, uint32_t *ctr, int tile_w, int tile_h, int packing, bool far,
+                              int grid, hipStream_t st) {
+    auto kernel = far ? batch_trace_kernel<true> : batch_trace_kernel<false>;
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(kBBlock), 0, st, views, t_first, t_tiles_x, nviews,
                        q_start, ctr, tile_w, tile_h, packing);
     return hipGetLastError();
 }
@@ -231,9 +233,10 @@ hipError_t launch_batch_reuse(const BatchView *views, const uint32_t *r_first, i
     return hipGetLastError();
 }
 
-int batch_trace_blocks_per_cu() {
+int batch_trace_blocks_per_cu(bool far) {
     int n = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, batch_trace_kernel, kBBlock, 0) != hipSuccess || n < 1)
+    auto kernel = far ? batch_trace_kernel<true> : batch_trace_kernel<false>;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, kernel, kBBlock, 0) != hipSuccess || n < 1)
         n = 1;
     return n;
 }

@@ -33,15 +33,16 @@ constexpr int kQueueStride = 32;
 constexpr int kQueueWords = 16 * kQueueStride;
 
 hipError_t launch_batch_reset(uint32_t *ctr, hipStream_t st);
+// far: some AO view's hierarchy has more than kNearNodes nodes (trace_pixel's FAR)
 hipError_t launch_batch_trace(const BatchView *views, const uint32_t *t_first, const uint32_t *t_tiles_x, int nviews,
-                              const uint32_t *q_start, uint32_t *ctr, int tile_w, int tile_h, int packing, int grid,
-                              hipStream_t st);
+                              const uint32_t *q_start, uint32_t *ctr, int tile_w, int tile_h, int packing, bool far,
+                              int grid, hipStream_t st);
 hipError_t launch_batch_reuse(const BatchView *views, const uint32_t *r_first, int nviews, const uint32_t *q_start,
                               uint32_t *ctr, size_t lds_bytes, int grid, hipStream_t st);
 // Resident blocks per CU of the two kernels (occupancy query).  The reuse
 // query also raises the kernel's dynamic-LDS limit to lds_bytes (call it
 // before launching or capturing); it returns 0 if that fails.
-int batch_trace_blocks_per_cu();
+int batch_trace_blocks_per_cu(bool far);
 int batch_reuse_blocks_per_cu(size_t lds_bytes);
 // Dynamic LDS the batched reuse kernel needs for a window view.
 size_t batch_reuse_lds(int radius, int mode, bool unbiased, int words);

@@ -45,6 +45,13 @@ constexpr int kMaxDepth = (kStackTotal - 1) / 3;
 // the halo saves.
 constexpr int kWTX = 16, kWTY = 16;
 
+// Most nodes of a hierarchy whose byte offsets fit 32 bits: the collecting walk
+// reads a per-lane node at one 32-bit offset from the array's (scalar) base,
+// which takes a register where a 64-bit address per row takes two (72
+// registers, 7 waves per SIMD, instead of 84 and 5).  Larger hierarchies
+// (beyond ~100 million triangles) take `traverse`.
+constexpr int64_t kNearNodes = (int64_t)1 << 25;
+
 struct DeviceBVH {
     const Node4 *nodes;
     const float4 *tris;  // 3 per triangle

@@ -39,6 +39,7 @@ struct ocr_plan {
     int64_t pixels = 0, trace_items = 0, reuse_items = 0;
     size_t reuse_lds = 0;
     int cus = 256, trace_bpc = 1, reuse_bpc = 1;
+    bool far = false;  // an AO view's hierarchy has more than kNearNodes nodes
     ocr_plan_tuning tun{};
     int tuned = 0, candidates = 0, from_cache = 0;
     double tune_ms = 0.0, best_trace_ms = 0.0;
@@ -102,7 +103,7 @@ hipError_t enqueue_trace(ocr_plan *p, hipStream_t st) {
     // one wave per item, four waves per block
     int grid = grid_of(p->cus, p->trace_bpc, (p->trace_items + 3) / 4);
     return launch_batch_trace(p->d_views, p->d_tfirst, p->d_ttx, p->nviews, p->d_qstart, p->d_ctr, p->tun.tile_w,
-                              p->tun.tile_h, p->tun.packing, grid, st);
+                              p->tun.tile_h, p->tun.packing, p->far, grid, st);
 }
 
 hipError_t enqueue_all(ocr_plan *p, hipStream_t st) {
@@ -416,7 +417,8 @@ ocr_status ocr_plan_create(const ocr_view_desc *views, int32_t nviews, const ocr
     int dev_cus = 0;
     if (hipDeviceGetAttribute(&dev_cus, hipDeviceAttributeMultiprocessorCount, p->device) == hipSuccess && dev_cus > 0)
         p->cus = dev_cus;
-    p->trace_bpc = batch_trace_blocks_per_cu();
+    for (const ocr_view_desc &d : p->desc) p->far |= d.mode == OCR_AO && d.bvh->dev.nnodes > kNearNodes;
+    p->trace_bpc = batch_trace_blocks_per_cu(p->far);
     if (p->reuse_items > 0) {
         p->reuse_bpc = batch_reuse_blocks_per_cu(std::max<size_t>(p->reuse_lds, 16));
         if (p->reuse_bpc < 1) {

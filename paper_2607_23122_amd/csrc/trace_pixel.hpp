@@ -22,21 +22,21 @@ __device__ inline void load3(const float *p, int64_t i, float v[3]) {
 // the same closest hit).  Shadow rays take one wave-coherent walk.  With
 // COUNT every ray takes the per-lane walk from the root, whose work is added
 // to *ws.  LT: one light (LightF) or several (LightSetF, shadows).
-template <int MODE, bool COUNT = false, class LT = LightF>
+template <int MODE, bool COUNT = false, class LT = LightF, bool FAR = false>
 __device__ inline void trace_pixel(const DeviceBVH &bvh, const GBufView &g, float R, const LT &L, uint32_t sd,
                                    uint32_t sample, const OccView &out, int px, int py, bool inside,
                                    uint32_t *stack, int stride, uint32_t *wstack, WalkStats *ws = nullptr) {
     const int64_t i = inside ? (int64_t)py * g.w + px : 0;
     const uint32_t prim = inside ? g.prim[i] : OCR_HIT_MISS;
     uint32_t code = OCR_HIT_MISS;  // background, or a shadow sample that is not traced
-    float d[3] = {0.f, 0.f, 0.f};
+    float o[3] = {0.f, 0.f, 0.f}, d[3] = {0.f, 0.f, 0.f};
     const float tmax = MODE == OCR_AO ? R : 1.0f;
     bool want = false;
     TRay r{};
     // the segment's box, for the AO walks' common entry node
     float slo[3] = {INFINITY, INFINITY, INFINITY}, shi[3] = {-INFINITY, -INFINITY, -INFINITY};
     if (prim != OCR_HIT_MISS) {
-        float x[3], n[3], o[3];
+        float x[3], n[3];
         load3(g.pos, i, x);
         load3(g.nrm, i, n);
         offset_point(x, n, o);
@@ -54,7 +54,7 @@ __device__ inline void trace_pixel(const DeviceBVH &bvh, const GBufView &g, floa
             if (!want) code = OCR_HIT_SELF;
         }
         if (want) {
-            make_ray(o, d, prim, OCR_HIT_MISS, tmax, r);
+            if (COUNT || FAR || MODE != OCR_AO) make_ray(o, d, prim, OCR_HIT_MISS, tmax, r);
             for (int c = 0; c < 3; ++c) {
                 const float e = __fmaf_rn(d[c], tmax, o[c]);
                 slo[c] = fminf(o[c], e);
@@ -75,9 +75,14 @@ __device__ inline void trace_pixel(const DeviceBVH &bvh, const GBufView &g, floa
         // AO segments are short: the wave's walks start below the levels where
         // their common box meets one child only
         const uint32_t entry = MODE == OCR_AO && !COUNT ? wave_entry_node(bvh, slo, shi) : 0u;
-        if (want) h = traverse<false, MODE == OCR_AO, COUNT>(bvh, r, tmax, stack, stride, overflow, ws, entry);
+        if constexpr (COUNT || FAR) {
+            if (want) h = traverse<false, MODE == OCR_AO, COUNT>(bvh, r, tmax, stack, stride, overflow, ws, entry);
+        } else {
+            if (want) h = traverse_collect<true>(bvh, o, d, prim, tmax, stack, stride, overflow, entry);
+        }
     }
     if (wave_ballot(overflow) != 0ull) {
+        if (!COUNT && !FAR && MODE == OCR_AO && overflow) make_ray(o, d, prim, OCR_HIT_MISS, tmax, r);
         const Hit hw = traverse_wave_closest<MODE == OCR_AO>(bvh, r, tmax, overflow, wstack);
         if (overflow) h = hw;
     }

@@ -38,11 +38,10 @@ struct TRay {
     uint32_t ign0, ign1;
 };
 
-// tmax: the end of the ray's t range (sets the relative part of the slack).
-__device__ inline void make_ray(const float o[3], const float d[3], uint32_t ign0, uint32_t ign1, float tmax,
-                                TRay &r) {
+// The slab terms of the box tests.  tmax: the end of the ray's t range (sets
+// the relative part of the slack).
+__device__ inline void ray_slabs(const float o[3], const float d[3], float tmax, TRay &r) {
     for (int c = 0; c < 3; ++c) {
-        r.o[c] = o[c];
         float dc = fabsf(d[c]) < 1e-20f ? copysignf(1e-20f, d[c]) : d[c];
         r.inv[c] = 1.0f / dc;
         const float oi = o[c] * r.inv[c];
@@ -52,6 +51,11 @@ __device__ inline void make_ray(const float o[3], const float d[3], uint32_t ign
         r.off_lo[c] = -oi - s;
         r.off_hi[c] = -oi + s;
     }
+}
+
+// The origin and shear of the triangle tests.
+__device__ inline void ray_shear(const float o[3], const float d[3], uint32_t ign0, uint32_t ign1, TRay &r) {
+    for (int c = 0; c < 3; ++c) r.o[c] = o[c];
     float ax = fabsf(d[0]), ay = fabsf(d[1]), az = fabsf(d[2]);
     int kz = (ax > ay) ? (ax > az ? 0 : 2) : (ay > az ? 1 : 2);
     int kx = kz == 2 ? 0 : kz + 1;
@@ -70,6 +74,12 @@ __device__ inline void make_ray(const float o[3], const float d[3], uint32_t ign
     }
     r.ign0 = ign0;
     r.ign1 = ign1;
+}
+
+__device__ inline void make_ray(const float o[3], const float d[3], uint32_t ign0, uint32_t ign1, float tmax,
+                                TRay &r) {
+    ray_slabs(o, d, tmax, r);
+    ray_shear(o, d, ign0, ign1, r);
 }
 
 // Watertight triangle test.  Returns the ray parameter t (> 0) or -1.
@@ -228,6 +238,125 @@ __device__ inline Hit traverse(const DeviceBVH &bvh, const TRay &r, float tmax, 
         if (sp == 0) break;
         --sp;
         node = lds_stack[sp * stride];
+    }
+    return h;
+}
+
+// 16 bytes of a node: row `row` (a constant), merged with `at` (0 or 16).
+__device__ inline float4 node_row(const DeviceBVH &bvh, uint32_t node, uint32_t at, int row) {
+    return *reinterpret_cast<const float4 *>(reinterpret_cast<const char *>(bvh.nodes) + ((node << 7) | at) + row);
+}
+
+// Closest hit over t in (0, tmax] (INCLUSIVE) or (0, tmax) for rays that most
+// often hit nothing (short AO rays in random directions), in two phases: the
+// lane visits the interior nodes its ray meets and collects their leaves, then
+// tests the leaves' triangles.  A wave of such rays is bound by the VALU
+// instructions of its steps, and a step that handles a node or a leaf per lane
+// pays for both in nearly every step (some lane always holds a leaf).  Apart,
+// every step of the first phase is a node and every step of the second a
+// triangle.  A node costs less as well: a lane reads the near and the far
+// planes of an axis at addresses chosen by its direction's sign (no min/max
+// per plane), and the children met are not sorted (nearest first pays only for
+// a ray that hits).  The closest (t, triangle id) does not depend on the
+// visiting order, so the result is traverse<false, INCLUSIVE>'s.
+// 1080p AO trace: 0.343 -> 0.307 ms (32% fewer VALU instructions a launch; the
+// rest is the L1 rate of the per-lane node reads), with one-wave blocks 0.297.
+//
+// `col` is the lane's column of kStackLds entries in LDS, `stride` words apart:
+// nodes grow from its start, leaves from its end.  When the two are about to
+// meet, the leaves are tested first; if the nodes alone leave no room, the walk
+// stops, sets `overflow` and its result is not to be used.  At most kNearNodes
+// nodes.  The triangle tests' shear terms are formed where they are used, so that they
+// take no registers in the first phase.
+template <bool INCLUSIVE>
+__device__ inline Hit traverse_collect(const DeviceBVH &bvh, const float o[3], const float d[3], uint32_t ign0,
+                                       float tmax, uint32_t *col, int stride, bool &overflow, uint32_t start) {
+    Hit h;
+    h.t = tmax;
+    h.tri = OCR_HIT_MISS;
+    h.leaf_tri = 0;
+    const float grow = 1.0f + 0x1p-20f;
+    // byte offsets of the near planes within an axis's pair of plane rows (the
+    // far ones are at 16 - near), and the offsets that go with them
+    uint32_t near_at[3];
+    float off_n[3], off_f[3];
+    TRay r;
+    ray_slabs(o, d, tmax, r);
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        const bool up = r.inv[c] > 0.0f;
+        near_at[c] = up ? 0u : 16u;
+        off_n[c] = up ? r.off_lo[c] : r.off_hi[c];
+        off_f[c] = up ? r.off_hi[c] : r.off_lo[c];
+    }
+    int sa = 0, la = kStackLds;  // nodes in [0, sa), leaves in [la, kStackLds)
+    uint32_t node = start;
+    bool walking = true;
+    for (;;) {
+        while (walking && la - sa >= 4) {
+            // the near planes of x, y, z, then the far ones (the other row of a
+            // pair), then the links
+            const float4 nx = node_row(bvh, node, near_at[0], 0), fx = node_row(bvh, node, near_at[0] ^ 16u, 0);
+            const float4 ny = node_row(bvh, node, near_at[1], 32), fy = node_row(bvh, node, near_at[1] ^ 16u, 32);
+            const float4 nz = node_row(bvh, node, near_at[2], 64), fz = node_row(bvh, node, near_at[2] ^ 16u, 64);
+            const float4 lk = node_row(bvh, node, 0u, 96);
+            const uint4 ch = {__float_as_uint(lk.x), __float_as_uint(lk.y), __float_as_uint(lk.z), __float_as_uint(lk.w)};
+            const float nxs[4] = {nx.x, nx.y, nx.z, nx.w}, fxs[4] = {fx.x, fx.y, fx.z, fx.w};
+            const float nys[4] = {ny.x, ny.y, ny.z, ny.w}, fys[4] = {fy.x, fy.y, fy.z, fy.w};
+            const float nzs[4] = {nz.x, nz.y, nz.z, nz.w}, fzs[4] = {fz.x, fz.y, fz.z, fz.w};
+            const uint32_t chs[4] = {ch.x, ch.y, ch.z, ch.w};
+            const float tlim = h.t * grow;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const float tnear = fmaxf(fmaxf(__fmaf_rn(nxs[i], r.inv[0], off_n[0]), __fmaf_rn(nys[i], r.inv[1], off_n[1])),
+                                          fmaxf(__fmaf_rn(nzs[i], r.inv[2], off_n[2]), 0.0f));
+                const float tfar = fminf(fminf(__fmaf_rn(fxs[i], r.inv[0], off_f[0]), __fmaf_rn(fys[i], r.inv[1], off_f[1])),
+                                         fminf(__fmaf_rn(fzs[i], r.inv[2], off_f[2]), tlim));
+                // (an empty slot's planes are far beyond near: never met, unless
+                // the ray is not finite; its link then counts as a leaf)
+                const bool met = tnear <= tfar, leaf = (int32_t)chs[i] < 0;
+                col[(leaf ? la - 1 : sa) * stride] = chs[i];  // kept if the counter below moves
+                sa += met && !leaf ? 1 : 0;
+                la -= met && leaf ? 1 : 0;
+            }
+            walking = sa > 0;
+            if (walking) node = col[--sa * stride];
+        }
+        if (la < kStackLds) ray_shear(o, d, ign0, OCR_HIT_MISS, r);
+        uint32_t cur = 0, end = 0;
+        for (;;) {
+            if (cur == end) {
+                if (la == kStackLds) break;
+                const uint32_t e = col[la * stride];
+                ++la;
+                if (e == kEmpty) continue;
+                cur = e & 0x07FFFFFFu;
+                end = cur + ((e >> 27) & 0xFu) + 1u;
+            }
+            const float4 *tp = bvh.tris + 3 * (size_t)cur;
+            const float4 v0 = tp[0], v1 = tp[1], v2 = tp[2];
+            const uint32_t id = __float_as_uint(v0.w);
+            if (id != ign0) {
+                const float t = tri_hit(r, v0, v1, v2);
+                if (t > 0.0f) {
+                    bool take;
+                    if (t < h.t) take = true;
+                    else if (t == h.t) take = h.tri == OCR_HIT_MISS ? INCLUSIVE : id < h.tri;
+                    else take = false;
+                    if (take) {
+                        h.t = t;
+                        h.tri = id;
+                        h.leaf_tri = cur;
+                    }
+                }
+            }
+            ++cur;
+        }
+        if (!walking) break;
+        if (kStackLds - sa < 4) {
+            overflow = true;
+            break;
+        }
     }
     return h;
 }
