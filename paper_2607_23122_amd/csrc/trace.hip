@@ -4,6 +4,7 @@
 #include "ocr_common.hpp"
 #include "trace_pixel.hpp"
 #include "traverse.hpp"
+#include "validate.hpp"
 
 namespace ocr {
 
@@ -155,7 +156,6 @@ __global__ __launch_bounds__(kBlock) void trace_count_kernel(DeviceBVH bvh, GBuf
 // (padded to a cache line each), then list x at offset x * per_xcd.  Only
 // candidates' validation words are ever read, so other pixels' words are
 // left as they are.
-constexpr int kCountStride = 32;  // uint32 per counter: one 128-byte line
 constexpr int kCompactTiles = 4;  // tiles per compaction block
 
 __global__ __launch_bounds__(kBlock) void clear_count_kernel(uint32_t *lists) {
@@ -210,27 +210,6 @@ __global__ __launch_bounds__(kBlock) void compact_kernel(GBufView g, OccView occ
     }
 }
 
-constexpr int kMaxPairs = 33 * 33;             // (4r+1)^2 at r = 8
-constexpr int kMaxWords = (kMaxPairs + 31) / 32;
-
-// receiver k of candidate j at pair index q, its offset point and the segment
-// vector w = z_j - o_k; false if k is outside the image or background
-__device__ inline bool pair_receiver(const GBufView &g, int jx, int jy, int side, float inv_side, int D, int q,
-                                     int64_t &k, uint32_t &primk, float ok[3], float nk[3]) {
-    const int qy = small_div(q, inv_side);
-    const int kx = jx + (q - qy * side) - D, ky = jy + qy - D;
-    if (kx < 0 || kx >= g.w || ky < 0 || ky >= g.h) return false;
-    k = (int64_t)ky * g.w + kx;
-    // the three loads issue together; background is decided afterwards
-    float xk[3];
-    primk = g.prim[k];
-    load3(g.pos, k, xk);
-    load3(g.nrm, k, nk);
-    if (primk == OCR_HIT_MISS) return false;
-    offset_point(xk, nk, ok);
-    return true;
-}
-
 // First-hit validation (Eq. occ-first-hit) for the sliding window.  The
 // receivers k = j + (q % side - D, q / side - D), side = 2D + 1, D = 2r, of a
 // candidate j whose density of z_j is positive are gathered (lane q of each
@@ -262,17 +241,6 @@ constexpr int kLightRun = 6;                   // candidates per run, light effe
 constexpr int kAoRun = 4;                      // candidates per run, AO
 constexpr int kGroupAoRun = 8;                 // candidates per run, fixed groups, AO
 constexpr int kGroupLightRun = 16;             // candidates per run, fixed groups, light effects
-constexpr int kRunWords = 128;                 // validation words of a run in LDS
-constexpr uint32_t kRunBlock = 256;            // consecutive runs an XCD takes at a time
-static_assert(kRunWords >= kMaxWords, "a run holds at least one candidate's words");
-
-// A candidate of the current run, as its walks need it.
-struct RunCand {
-    float oj[3], dzj[3];
-    int32_t jx, jy;
-    uint32_t hj;
-    int32_t pad;
-};
 
 // COUNT: the work-accounting instantiation (lane-masked walk, same bits),
 // which adds the segments' useful work to stats[0..4].  Bounded to 7 waves
@@ -406,19 +374,7 @@ __global__ __launch_bounds__(kBlock, 7) void validate_window_kernel(DeviceBVH bv
             // before this candidate's data is loaded, so that nothing of it
             // lives across the walk)
             if (count + npairs - 1 > kMaxPairs) flush(b);
-            // list x and the position in it of candidate c0 + b (scalar)
-            uint32_t off = c0 + (uint32_t)b, base = 8 * kCountStride;
-#pragma unroll
-            for (int x = 0; x < 7; ++x) {
-                const uint32_t n = lists[x * kCountStride];
-                if (off >= n) {
-                    off -= n;
-                    base += per_xcd;
-                } else {
-                    break;
-                }
-            }
-            const int64_t j = __builtin_amdgcn_readfirstlane((int)lists[base + off]);
+            const int64_t j = __builtin_amdgcn_readfirstlane((int)lists[list_at(lists, per_xcd, c0 + (uint32_t)b)]);
             const int jy = (int)((uint32_t)j / (uint32_t)g.w), jx = (int)j - jy * g.w;
             const uint32_t hj = occ.hit[j];
             float xj[3], nj[3], oj[3], dzj[3], nzj[3];
@@ -583,6 +539,26 @@ hipError_t launch_trace_count(const DeviceBVH &bvh, const GBufView &g, int mode,
     return hipGetLastError();
 }
 
+// Whether an AO window is validated by shafts (shaft.hip) rather than by the
+// walk above.  A shaft costs a candidate a gather and its triangles' rows
+// whatever its segments, the walk 64 segments at a time the nodes and triangles
+// on their way; so shafts pay with more segments per candidate (radius) and
+// longer walks (triangles), and in small frames, whose few waves wait for
+// memory: a shaft's loads are fewer and wider.  Measured, shaft / walk, ms:
+//   radius 3: 6146 triangles 1920x1080 1.29 / 1.48, 3074 1.11 / 1.10, 770 0.45 / 0.39;
+//             1.16M triangles 1.17 / 2.39
+//   radius 2: 49154 triangles 1920x1080 0.70 / 0.92, 12290 1.06 / 1.03, 770 0.37 / 0.24;
+//             1.16M triangles 0.88 / 1.38
+//   radius 1: 1.16M triangles 1920x1080 0.71 / 0.68, 1280x720 0.36 / 0.41, 320x180 0.09 / 0.17;
+//             49154 triangles 960x540 0.18 / 0.17
+//   small frames: 770 triangles 256x256 radius 2 0.037 / 0.044, 960x540 0.114 / 0.089;
+//             1152 triangles 320x180 radius 2 0.023 / 0.031
+static bool shaft_pays(const DeviceBVH &bvh, const GBufView &g, int radius) {
+    const int64_t px = (int64_t)g.w * g.h;
+    if (radius <= 1) return radius == 1 && bvh.ntris >= 65536 && px <= 1 << 20;
+    return bvh.ntris >= (radius == 2 ? 16384 : 4096) || px <= 1 << 17;
+}
+
 template <class LT>
 static hipError_t launch_validate_t(const DeviceBVH &bvh, const GBufView &g, const OccView &occ, int mode, float R,
                                     const LT &L, const ocr_reuse_params &p, uint32_t *bits, uint64_t *stats,
@@ -614,6 +590,8 @@ static hipError_t launch_validate_t(const DeviceBVH &bvh, const GBufView &g, con
         else OCR_VAL(M, false, G);      \
     } while (0)
     if (p.pattern == OCR_WINDOW) {
+        if (mode == OCR_AO && !stats && shaft_pays(bvh, g, p.radius))
+            return launch_validate_shaft(bvh, g, occ, R, D, words, bits, lists, per_xcd, st);
         if (mode == OCR_AO) OCR_VAL_M(OCR_AO, false);
         else OCR_VAL_M(OCR_SHADOW, false);
     } else {
