@@ -207,8 +207,8 @@ __global__ __launch_bounds__(kRBlock, 7) void batch_reuse_kernel(const BatchView
     }
 }
 
-size_t batch_reuse_lds(int radius, int mode, bool unbiased, int words) {
-    return win_layout(radius, mode, unbiased, words).total;
+size_t batch_reuse_lds(int radius, int mode, int words) {
+    return win_layout(radius, mode, mode != OCR_AO, words).total;
 }
 
 hipError_t launch_batch_reset(uint32_t *ctr, hipStream_t st) {

@@ -45,6 +45,6 @@ hipError_t launch_batch_reuse(const BatchView *views, const uint32_t *r_first, i
 int batch_trace_blocks_per_cu(bool far);
 int batch_reuse_blocks_per_cu(size_t lds_bytes);
 // Dynamic LDS the batched reuse kernel needs for a window view.
-size_t batch_reuse_lds(int radius, int mode, bool unbiased, int words);
+size_t batch_reuse_lds(int radius, int mode, int words);
 
 }  // namespace ocr

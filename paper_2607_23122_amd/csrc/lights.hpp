@@ -187,6 +187,57 @@ __device__ inline float inv_bilinear_q(const float w[3], const RecvBilin &rk, co
     return __builtin_amdgcn_rcpf(bilinear_q(rk, a, b));
 }
 
+// A bound on where dens_light can be positive, from the light-frame terms of z
+// and of a receiver alone.  The crossing's light coordinates satisfy
+//   a <n_L, w> = H a_k + U h_k,  b <n_L, w> = H b_k + V h_k,  <n_L, w> = H + h_k
+// with H, U, V the terms of z, so the support lies within |H a_k + U h_k|,
+// |H b_k + V h_k| <= |H + h_k| / 2.  The terms have the size of the distance to
+// the light, so these err more than dens_light, which has w itself: by at most
+// 2^-20 l q (q + q_z), where l is the light's longer edge and q bounds |o_k - c|
+// over the shorter edge (q_z for z).  The test allows four times that, with the
+// largest q of the tile's receivers, whatever the other support conditions.
+struct LightScale {
+    float g, asp, l;  // 1 / shorter edge, longer / shorter, longer
+};
+__device__ inline LightScale light_scale(const LightF &L) {
+    const float u = sqrtf(dot3f(L.eu, L.eu)), v = sqrtf(dot3f(L.ev, L.ev));
+    const float lo = fminf(u, v), hi = fmaxf(u, v);
+    return LightScale{1.0f / lo, hi / lo, hi};
+}
+__device__ inline float term_size(float h, float a, float b, const LightScale &s) {
+    return __fmaf_rn(s.g, fabsf(h), __fmaf_rn(s.asp, fabsf(a) + fabsf(b), 1.0f));
+}
+struct CandTerms {
+    float H, U, V, slack;
+};
+// rj: the light terms of the candidate's own point, z = o_j + dz_j; qmax: the
+// largest term_size of the receivers
+__device__ inline CandTerms cand_terms(const RecvShadow &rj, const float dzj[3], const LightF &L, float qmax) {
+    const LightScale s = light_scale(L);
+    CandTerms c;
+    c.H = dot3f(L.nl, dzj) - rj.hk;
+    c.U = dot3f(L.uhat, dzj) + rj.ak;
+    c.V = dot3f(L.vhat, dzj) + rj.bk;
+    c.slack = 0x1p-18f * s.l * qmax * (qmax + term_size(c.H, c.U, c.V, s));
+    return c;
+}
+__device__ inline bool may_support(const CandTerms &c, float hk, float ak, float bk) {
+    const float A = __fmaf_rn(c.H, ak, c.U * hk), B = __fmaf_rn(c.H, bk, c.V * hk);
+    return fmaxf(fabsf(A), fabsf(B)) <= __fmaf_rn(0.5001f, fabsf(c.H + hk), c.slack);
+}
+// term_size of a receiver (the largest over the lights)
+__device__ inline float recv_size(const float o[3], const LightF &L) {
+    const RecvShadow r = recv_shadow(o, L);
+    return term_size(r.hk, r.ak, r.bk, light_scale(L));
+}
+__device__ inline float recv_size(const float o[3], const LightSetF &S) {
+    float q = 0.0f;
+#pragma unroll
+    for (int l = 0; l < kMaxLights; ++l)
+        if (l < S.n) q = fmaxf(q, recv_size(o, S.l[l]));
+    return q;
+}
+
 // Floats of a receiver's light terms in LDS.
 template <class LT>
 constexpr int kRecvFloats = kBilinear<LT> ? 6 : 3;
@@ -239,6 +290,40 @@ __device__ inline float dens_light(const float w[3], const float nk[3], const Re
         if (k < S.n) p += dens_shadow(w, nk, recv_shadow(rk.o, S.l[k]), nz, S.l[k]);
     return p;
 }
+
+// The terms of a candidate staged in cell c (sh: the staged light terms, or
+// points for several lights, `cells` apart per component) ...
+__device__ inline void cell_terms(const float *sh, int cells, int c, const float dzj[3], const LightF &L, float qmax,
+                                  CandTerms (&t)[1]) {
+    t[0] = cand_terms(RecvShadow{sh[c], sh[cells + c], sh[2 * cells + c]}, dzj, L, qmax);
+}
+__device__ inline void cell_terms(const float *sh, int cells, int c, const float dzj[3], const LightSetF &S,
+                                  float qmax, CandTerms (&t)[kMaxLights]) {
+    const float oj[3] = {sh[c], sh[cells + c], sh[2 * cells + c]};
+#pragma unroll
+    for (int l = 0; l < kMaxLights; ++l)
+        if (l < S.n) t[l] = cand_terms(recv_shadow(oj, S.l[l]), dzj, S.l[l], qmax);
+}
+// ... and whether the receiver staged in cell k may have a positive density of
+// it (of any light).
+__device__ inline bool cell_support(const float *sh, int cells, int k, const LightF &, const CandTerms (&t)[1]) {
+    return may_support(t[0], sh[k], sh[cells + k], sh[2 * cells + k]);
+}
+__device__ inline bool cell_support(const float *sh, int cells, int k, const LightSetF &S,
+                                    const CandTerms (&t)[kMaxLights]) {
+    const float ok[3] = {sh[k], sh[cells + k], sh[2 * cells + k]};
+    bool any = false;
+#pragma unroll
+    for (int l = 0; l < kMaxLights; ++l) {
+        if (l < S.n) {
+            const RecvShadow r = recv_shadow(ok, S.l[l]);
+            any |= may_support(t[l], r.hk, r.ak, r.bk);
+        }
+    }
+    return any;
+}
+template <class LT>
+constexpr int kLightTerms = std::is_same<LT, LightSetF>::value ? kMaxLights : 1;
 
 __device__ inline float front_light(const float o[3], const float n[3], const LightF &L) {
     return front_fraction(o, n, L);

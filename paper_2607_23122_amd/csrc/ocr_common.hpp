@@ -176,16 +176,78 @@ __device__ inline int small_div(int q, float inv_d) { return (int)(((float)q + 0
 // in a vector register and compares it again.
 __device__ inline unsigned long long wave_ballot(bool p) { return __builtin_amdgcn_ballot_w64(p); }
 
-// Inclusive prefix sum over the wave's 64 lanes.
+// Inclusive prefix sum over the wave's 64 lanes: six adds with the earlier
+// lane's sum as a DPP operand (four within the rows of 16 lanes, then rows 0
+// and 2 into the next, then the lower half into the upper).
+template <int CTRL, int ROWS>
+__device__ inline int dpp_add(int v) {
+    return v + __builtin_amdgcn_update_dpp(0, v, CTRL, ROWS, 0xF, false);
+}
 __device__ inline int wave_incl_scan(int v) {
-    const int lane = threadIdx.x & 63;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        const int u = __shfl_up(v, d);
-        if (lane >= d) v += u;
-    }
+    v = dpp_add<0x111, 0xF>(v);  // row_shr:1, 2, 4, 8
+    v = dpp_add<0x112, 0xF>(v);
+    v = dpp_add<0x114, 0xF>(v);
+    v = dpp_add<0x118, 0xF>(v);
+    v = dpp_add<0x142, 0xA>(v);  // row_bcast:15 into rows 1 and 3
+    v = dpp_add<0x143, 0xC>(v);  // row_bcast:31 into rows 2 and 3
     return v;
 }
+
+// Inclusive running maximum over the wave of values >= 0.
+template <int CTRL, int ROWS>
+__device__ inline int dpp_max0(int v) {
+    return max(v, __builtin_amdgcn_update_dpp(0, v, CTRL, ROWS, 0xF, false));
+}
+__device__ inline int wave_incl_max(int v) {
+    v = dpp_max0<0x111, 0xF>(v);
+    v = dpp_max0<0x112, 0xF>(v);
+    v = dpp_max0<0x114, 0xF>(v);
+    v = dpp_max0<0x118, 0xF>(v);
+    v = dpp_max0<0x142, 0xA>(v);
+    v = dpp_max0<0x143, 0xC>(v);
+    return v;
+}
+
+// Position of the set bit number n (from 0) of b.
+__device__ inline int nth_bit(uint32_t b, int n) {
+    int at = 0;
+#pragma unroll
+    for (int s = 16; s >= 1; s >>= 1) {
+        const int m = __popc((b >> at) & ((1u << s) - 1u));
+        if (n >= m) {
+            n -= m;
+            at += s;
+        }
+    }
+    return at;
+}
+
+// Minimum / maximum over the wave as a scalar.  The floats are compared as
+// integers that order alike (negative ones with their lower bits flipped; a NaN
+// lies beyond the infinities), since an integer min or max takes the other
+// lane's value as a DPP operand of its own: six instructions, four steps
+// within the rows of 16 lanes and two across them, where a shuffle and a float
+// min per step take two and an LDS access.  Lane 63 holds the result.
+__device__ inline int ordered_int(float v) {
+    const int i = __builtin_bit_cast(int, v);
+    return i ^ ((i >> 31) & 0x7FFFFFFF);
+}
+template <int CTRL>
+__device__ inline int dpp_min(int v) {
+    return min(v, __builtin_amdgcn_update_dpp(0x7FFFFFFF, v, CTRL, 0xF, 0xF, false));
+}
+__device__ inline float from_ordered(int i) { return __builtin_bit_cast(float, i ^ ((i >> 31) & 0x7FFFFFFF)); }
+__device__ inline int wave_min_i(int v) {
+    v = dpp_min<0x111>(v);  // row_shr:1, 2, 4, 8
+    v = dpp_min<0x112>(v);
+    v = dpp_min<0x114>(v);
+    v = dpp_min<0x118>(v);
+    v = dpp_min<0x142>(v);  // row_bcast:15, 31
+    v = dpp_min<0x143>(v);
+    return __builtin_amdgcn_readlane(v, 63);
+}
+__device__ inline float wave_min_u(float f) { return from_ordered(wave_min_i(ordered_int(f))); }
+__device__ inline float wave_max_u(float f) { return -wave_min_u(-f); }
 
 // Make this wave's LDS writes visible to its other lanes before they read.
 __device__ inline void wave_sync() {

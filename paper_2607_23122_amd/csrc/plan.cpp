@@ -359,8 +359,7 @@ ocr_status ocr_plan_create(const ocr_view_desc *views, int32_t nviews, const ocr
         else racc += (uint64_t)((d.gbuf.width + kWTX - 1) / kWTX) * (uint64_t)((d.gbuf.height + kWTY - 1) / kWTY);
         if (d.params.estimator == OCR_UNBIASED) p->unb_views.push_back(v);
         if (!grp && d.params.estimator != OCR_NOREUSE)
-            p->reuse_lds = std::max(p->reuse_lds, batch_reuse_lds(d.params.radius, d.mode,
-                                                                  d.params.estimator == OCR_UNBIASED, hv[v].words));
+            p->reuse_lds = std::max(p->reuse_lds, batch_reuse_lds(d.params.radius, d.mode, hv[v].words));
     }
     rfirst[nviews] = (uint32_t)racc;
     p->reuse_items = (int64_t)racc;

@@ -42,7 +42,7 @@ static inline int r_grid_for(int ntiles) {
 }
 
 template <int MODE, bool UNB, class LT = LightF>
-__global__ __launch_bounds__(kRBlock) void reuse_window_kernel(GBufView g, OccView occ, float R2, LT L,
+__global__ __launch_bounds__(kWinMost, MODE == OCR_AO ? 1 : 6) void reuse_window_kernel(GBufView g, OccView occ, float R2, LT L,
                                                                const uint32_t *__restrict__ bits, int words, int R,
                                                                int dark_guard, int accumulate, float *out,
                                                                int tiles_x, int ntiles, float scale) {
@@ -221,12 +221,20 @@ __global__ void scale_kernel(float *out, int64_t n, float s) {
 // ---------------------------------------------------------------------------
 // launchers
 // ---------------------------------------------------------------------------
+// In frames of at most this many tiles the slowest tile's time is much of the
+// frame's, and eight waves share a tile's candidates instead of four (window 3,
+// 4 / 8 waves: 256x256 AO 17.5 / 11.6 us, boxes 31 / 19; 1280x720 AO 45 / 40,
+// shadows 128 / 102; at 1080p AO 120 / 120, shadows 200 / 211).
+constexpr int kFewTiles = 4096;
+
 template <int MODE, bool UNB, class LT>
 static hipError_t launch_win(const GBufView &g, const OccView &occ, float R2, const LT &L, const uint32_t *bits,
                              int words, const ocr_reuse_params &p, float *out, float scale, hipStream_t st) {
     int tiles_x = (g.w + kWTX - 1) / kWTX, tiles_y = (g.h + kWTY - 1) / kWTY;
     int nt = tiles_x * tiles_y;
-    WinLayout lay = win_layout(p.radius, MODE, UNB, words, kRecvFloats<LT>);
+    // (row-task radii; the others' per-wave scratch would take the LDS)
+    const int lanes = nt <= kFewTiles && row_body_radius(p.radius) ? kWinMost : kRBlock;
+    WinLayout lay = win_layout(p.radius, MODE, kPairBody<MODE, UNB, LT>, words, kRecvFloats<LT>, lanes / 64);
     // dynamic-LDS limit raised so far (64 KB by default); several host
     // threads may launch at once
     static std::atomic<size_t> attr_bytes{64 * 1024};
@@ -238,7 +246,7 @@ static hipError_t launch_win(const GBufView &g, const OccView &occ, float R2, co
         while (cur < lay.total && !attr_bytes.compare_exchange_weak(cur, lay.total)) {
         }
     }
-    dim3 grid(r_grid_for(nt)), block(kRBlock);
+    dim3 grid(r_grid_for(nt)), block(lanes);
     hipLaunchKernelGGL((reuse_window_kernel<MODE, UNB, LT>), grid, block, lay.total, st, g, occ, R2, L, bits, words,
                        p.radius, p.dark_guard, p.accumulate, out, tiles_x, nt, scale);
     return hipSuccess;

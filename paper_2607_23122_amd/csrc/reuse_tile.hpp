@@ -28,10 +28,25 @@
 
 namespace ocr {
 
-constexpr int kRBlock = 256;
+constexpr int kRBlock = 256;     // lanes of a group or per-pixel block, and of a window tile's block
+constexpr int kWinMost = 512;    // most lanes of a window tile's block
 // A candidate with at most this many positive densities in its rectangle takes
 // the sparse path of the scatter.
 constexpr int kSparse = 8;
+// Row-task radii, light effects: a candidate with at most this many receivers
+// that may have a positive density is summed pair by pair.  (A pair's sum grows
+// with the candidate's pairs, a row task's cost with the rows of the square:
+// radius 1 / 2 / 3 unbiased shadows at 1080p 59 / 79 / 135 us with 10 pairs for
+// all, 76 / 92 / 137 with 16, 92 / 126 / 164 with 24.)
+__host__ __device__ constexpr int few_pairs(int R) { return 4 * R; }
+// Which light effects do: several lights' marks cost nearly their densities, so
+// they are left to the row tasks unless validation bits mark the pairs (two
+// lights biased at 1080p 0.50 ms by row tasks, 0.58 by pairs).
+template <int MODE, bool UNB, class LT>
+constexpr bool kPairBody = MODE != OCR_AO && (UNB || !std::is_same<LT, LightSetF>::value);
+// Counters ahead of the candidate list: candidates, cursor, largest term_size
+// (as its bits), candidates left to the row tasks, their cursor.
+constexpr int kListHead = 8;
 
 __device__ inline void ld3(const float *p, int64_t i, float v[3]) {
     v[0] = p[3 * i];
@@ -94,7 +109,7 @@ __host__ __device__ constexpr bool row_body_radius(int R) { return R >= 1 && R <
 // LDS layout of the window kernel for radius R (dynamic shared memory).
 struct WinLayout {
     int RWX, RWY, cells, side, dens, hsum, words;
-    size_t o_off, n_off, sh_off, valid_off, miss_off, list_off, B_off, wave_off, total;
+    size_t o_off, n_off, sh_off, valid_off, miss_off, list_off, many_off, B_off, wave_off, total;
 };
 
 __host__ __device__ constexpr size_t lds_take(size_t &off, size_t bytes) {
@@ -103,8 +118,10 @@ __host__ __device__ constexpr size_t lds_take(size_t &off, size_t bytes) {
     return at;
 }
 
-// nrecv: floats of a receiver's light terms (kRecvFloats of the light type).
-__host__ __device__ constexpr WinLayout win_layout(int R, int mode, bool unb, int words, int nrecv = 3) {
+// nrecv: floats of a receiver's light terms (kRecvFloats of the light type);
+// waves: of the block; pairs: kPairBody of the kernel.
+__host__ __device__ constexpr WinLayout win_layout(int R, int mode, bool pairs, int words, int nrecv = 3,
+                                                   int waves = kRBlock / 64) {
     WinLayout l{};
     l.RWX = kWTX + 2 * R;
     l.RWY = kWTY + 2 * R;
@@ -120,11 +137,13 @@ __host__ __device__ constexpr WinLayout win_layout(int R, int mode, bool unb, in
     l.sh_off = lds_take(off, mode != OCR_AO ? sizeof(float) * nrecv * l.cells : 0);
     l.valid_off = lds_take(off, l.cells);
     l.miss_off = lds_take(off, l.cells);
-    l.list_off = lds_take(off, 4 * sizeof(int) + sizeof(uint16_t) * l.cells);
+    l.list_off = lds_take(off, kListHead * sizeof(int) + sizeof(uint16_t) * l.cells);
+    // the candidates that the pair lanes leave to the row tasks
+    l.many_off = lds_take(off, row_body_radius(R) && pairs ? sizeof(uint16_t) * l.cells : 0);
     // per-wave scratch: the per-candidate body's densities and box sums (the
-    // row-task body keeps its sums in registers)
-    const int per_wave = row_body_radius(R) ? 0 : l.dens + l.hsum;
-    l.wave_off = lds_take(off, sizeof(float) * (kRBlock / 64) * per_wave);
+    // row-task body keeps its sums in registers), the pair lanes' candidates
+    const int per_wave = !row_body_radius(R) ? l.dens + l.hsum : (pairs ? 64 : 0);
+    l.wave_off = lds_take(off, sizeof(float) * waves * per_wave);
     l.total = off;
     return l;
 }
@@ -202,13 +221,14 @@ __device__ inline float from_prev_lane(float v) {
 template <int MODE, bool UNB, class LT, int R>
 __device__ inline void tile_row_candidates(const WinLayout &lay, unsigned char *smem, const GBufView &g,
                                            const OccView &occ, float R2, const LT &L,
-                                           const uint32_t *__restrict__ bits, int words, int tx, int ty) {
+                                           const uint32_t *__restrict__ bits, int words, int tx, int ty,
+                                           const uint16_t *s_list, const int *s_end, int *s_cursor) {
     constexpr int TW = 2 * R + 1, SIDE = 4 * R + 1, D = 2 * R;
     constexpr int TX = kWTX, TY = kWTY, RW = kWTX + 2 * R, CELLS = RW * (kWTY + 2 * R);
     // The staged normals and light terms follow the positions directly
     // (3 * CELLS floats each, a multiple of 16 bytes), so all the receiver
     // values a density reads sit at constant offsets from one LDS address.
-    constexpr WinLayout kLay = win_layout(R, MODE, UNB, 1, kRecvFloats<LT>);
+    constexpr WinLayout kLay = win_layout(R, MODE, kPairBody<MODE, UNB, LT>, 1, kRecvFloats<LT>);
     static_assert(kLay.cells == CELLS && kLay.n_off == kLay.o_off + 3 * CELLS * sizeof(float) &&
                       (MODE == OCR_AO || kLay.sh_off == kLay.n_off + 3 * CELLS * sizeof(float)),
                   "receiver arrays are contiguous");
@@ -217,15 +237,12 @@ __device__ inline void tile_row_candidates(const WinLayout &lay, unsigned char *
     const float *s_o = reinterpret_cast<const float *>(smem + lay.o_off);
     const float *s_n = s_o + 3 * CELLS;
     const float *s_sh = s_n + 3 * CELLS;
-    int *s_count = reinterpret_cast<int *>(smem + lay.list_off);
-    const uint16_t *s_list = reinterpret_cast<const uint16_t *>(smem + lay.list_off + 4 * sizeof(int));
     const int lane = threadIdx.x & 63;
     const int x0 = tx * TX - R, y0 = ty * TY - R;
-    // s_count[0]: candidates listed; s_count[1]: the shared cursor (entries
-    // claimed), zero at the tile's start
-    const int end = s_count[0];
+    // candidates s_list[0, *s_end), and the shared cursor (entries claimed)
+    const int end = *s_end;
     for (;;) {
-        const int cur = __builtin_amdgcn_readfirstlane(__atomic_load_n(&s_count[1], __ATOMIC_RELAXED));
+        const int cur = __builtin_amdgcn_readfirstlane(__atomic_load_n(s_cursor, __ATOMIC_RELAXED));
         if (cur >= end) break;
         // candidate lanes: lane k holds candidate cur + k and its receiver
         // rows; the batch is the leading candidates whose rows fit
@@ -243,7 +260,7 @@ __device__ inline void tile_row_candidates(const WinLayout &lay, unsigned char *
         // claim the batch; if another wave moved the cursor first, form the
         // next batch from where it now stands (some wave succeeds each round)
         int won = 0;
-        if (lane == 0) won = atomicCAS(&s_count[1], cur, cur + nb) == cur;
+        if (lane == 0) won = atomicCAS(s_cursor, cur, cur + nb) == cur;
         if (!__builtin_amdgcn_readfirstlane(won)) continue;
 
         // this lane's candidate and receiver row
@@ -279,7 +296,10 @@ __device__ inline void tile_row_candidates(const WinLayout &lay, unsigned char *
             const int kcb = __mul24(ky, RW) + kx0;
 #pragma unroll
             for (int e = 0; e < SIDE; ++e) {
-                if (e < WD && ((rowbits >> e) & 1u)) {
+                // (candidates left by the pair body have many positive
+                // densities: all are evaluated, without a branch for each)
+                const bool on = e < WD && ((rowbits >> e) & 1u);
+                if (kPairBody<MODE, UNB, LT> || on) {
                     const int kc = kcb + e;
                     const float ok[3] = {s_o[kc], s_o[CELLS + kc], s_o[2 * CELLS + kc]};
                     const float nk[3] = {s_n[kc], s_n[CELLS + kc], s_n[2 * CELLS + kc]};
@@ -290,7 +310,8 @@ __device__ inline void tile_row_candidates(const WinLayout &lay, unsigned char *
                     } else {
                         float v[kRecvFloats<LT>];
                         for (int a = 0; a < kRecvFloats<LT>; ++a) v[a] = s_sh[a * CELLS + kc];
-                        p[e] = dens_light(w, nk, recv_load(v, L), nzj, L);
+                        const float d = dens_light(w, nk, recv_load(v, L), nzj, L);
+                        p[e] = on ? d : 0.0f;
                     }
                 }
             }
@@ -332,6 +353,226 @@ __device__ inline void tile_row_candidates(const WinLayout &lay, unsigned char *
     (void)TY;
 }
 
+// The light effects' candidates with few positive densities, row-task radii.
+// The light subtends a narrow cone at z_j, so most candidates have one or two
+// among their (4R + 1)^2 densities, and only those receivers are targets with a
+// term.  First a lane takes a candidate and marks the receivers that may have a
+// positive density (unbiased: the validation bits; biased: may_support, 10 VALU
+// instructions and 3 LDS values a receiver instead of 45 and 9).  Then a lane
+// takes a marked pair, the pairs of a candidate on consecutive lanes in row and
+// column order: it evaluates the density and sums P_i(j) over the candidate's
+// pairs in the target's window, row by row, by cross-lane reads: the box sums
+// without their zeros, so the same bits.  Candidates with more than few_pairs(R)
+// marks are listed in s_many for the row tasks.
+// 1080p, window 3, one light: biased 0.275 -> 0.200 ms (1.41e8 -> 0.67e8 VALU
+// instructions), unbiased 0.207 -> 0.137 (0.24e8).  What is left is the tail:
+// without the few tiles that hold hundreds of candidates for the row tasks
+// (9500 of 882000), which take 100 us each, the unbiased launch would end after
+// 40 us.
+template <int MODE, bool UNB, class LT, int R>
+__device__ inline void tile_pair_candidates(const WinLayout &lay, unsigned char *smem, const GBufView &g,
+                                            const OccView &occ, const LT &L, const uint32_t *__restrict__ bits,
+                                            int words, int tx, int ty) {
+    constexpr int SIDE = 4 * R + 1, D = 2 * R, NW = (SIDE * SIDE + 31) / 32;
+    constexpr int TX = kWTX, TY = kWTY, RW = kWTX + 2 * R, RH = kWTY + 2 * R, CELLS = RW * RH;
+    constexpr float kInvRw = 1.0f / (float)RW, kInvSide = 1.0f / (float)SIDE;
+    unsigned long long *s_B = reinterpret_cast<unsigned long long *>(smem + lay.B_off);
+    const float *s_o = reinterpret_cast<const float *>(smem + lay.o_off);
+    const float *s_n = reinterpret_cast<const float *>(smem + lay.n_off);
+    const float *s_sh = reinterpret_cast<const float *>(smem + lay.sh_off);
+    int *s_count = reinterpret_cast<int *>(smem + lay.list_off);
+    const uint16_t *s_list = reinterpret_cast<const uint16_t *>(smem + lay.list_off + kListHead * sizeof(int));
+    uint16_t *s_many = reinterpret_cast<uint16_t *>(smem + lay.many_off);
+    int *l_own = reinterpret_cast<int *>(smem + lay.wave_off) + (threadIdx.x >> 6) * 64;
+    const int lane = threadIdx.x & 63;
+    const int x0 = tx * TX - R, y0 = ty * TY - R;
+    const int ncand = s_count[0];
+    const float qmax = __int_as_float(s_count[2]);
+    for (;;) {
+        int base = 0;
+        if (lane == 0) base = atomicAdd(&s_count[1], 64);
+        base = __builtin_amdgcn_readfirstlane(base);
+        if (base >= ncand) break;
+        const bool has = base + lane < ncand;
+        const int c = s_list[has ? base + lane : base];
+        const int cy = small_div(c, kInvRw), cx = c - __mul24(cy, RW);
+        const int64_t gj = (int64_t)(y0 + cy) * g.w + (x0 + cx);
+        // marked receivers: bit q for cell (cx - D + q % SIDE, cy - D + q / SIDE)
+        uint32_t w[NW];
+        if constexpr (UNB) {
+#pragma unroll
+            for (int i = 0; i < NW; ++i) w[i] = bits[gj * words + i];
+        } else {
+#pragma unroll
+            for (int i = 0; i < NW; ++i) w[i] = 0u;
+            float dzj[3];
+            ld3(occ.dz, gj, dzj);
+            CandTerms t[kLightTerms<LT>];
+            cell_terms(s_sh, CELLS, c, dzj, L, qmax, t);
+#pragma unroll 1
+            for (int y = 0; y < SIDE; ++y) {
+                // (a row outside the staged cells is read from the nearest one
+                // and masked below; a column beyond them reads a neighbour row)
+                const int k0 = __mul24(min(max(cy - D + y, 0), RH - 1), RW) + (cx - D);
+                uint32_t m = 0;
+#pragma unroll
+                for (int e = 0; e < SIDE; ++e) m |= cell_support(s_sh, CELLS, k0 + e, L, t) ? 1u << e : 0u;
+                // the row's bits enter above the earlier ones
+#pragma unroll
+                for (int i = 0; i < NW - 1; ++i) w[i] = __builtin_amdgcn_alignbit(w[i + 1], w[i], SIDE);
+                w[NW - 1] = (w[NW - 1] >> SIDE) | (m << (32 - SIDE));
+            }
+            // down to bit 0
+            constexpr int kRest = 32 * NW - SIDE * SIDE;
+#pragma unroll
+            for (int i = 0; i < NW - 1; ++i) w[i] = __builtin_amdgcn_alignbit(w[i + 1], w[i], kRest);
+            w[NW - 1] >>= kRest;
+        }
+        // the receivers that the candidate's targets of this tile need
+        const CandRect q = cand_rect(cx, cy, R);
+        const int ra = q.ty0 - R - (cy - D), rb = ra + q.nty + 2 * R;  // rows [ra, rb) of the square
+        const uint32_t cols = ((1u << (q.ntx + 2 * R)) - 1u) << (q.tx0 - R - (cx - D));
+        uint32_t keep[NW + 1];
+#pragma unroll
+        for (int i = 0; i <= NW; ++i) keep[i] = 0u;
+#pragma unroll
+        for (int y = 0; y < SIDE; ++y) {
+            const uint32_t row = y >= ra && y < rb ? cols : 0u;
+            const int i = (y * SIDE) >> 5, sh = (y * SIDE) & 31;
+            keep[i] |= row << sh;
+            if (sh + SIDE > 32) keep[i + 1] |= row >> ((32 - sh) & 31);
+        }
+        int cnt = 0;
+#pragma unroll
+        for (int i = 0; i < NW; ++i) {
+            w[i] = has ? w[i] & keep[i] : 0u;
+            cnt += __popc(w[i]);
+        }
+        const bool many = cnt > few_pairs(R);
+        const unsigned long long mm = wave_ballot(many);
+        if (mm != 0ull) {
+            int at = 0;
+            if (lane == 0) at = atomicAdd(&s_count[3], (int)__popcll(mm));
+            at = __builtin_amdgcn_readfirstlane(at);
+            if (many) {
+                s_many[at + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mm >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mm, 0u))] = (uint16_t)c;
+                cnt = 0;
+            }
+        }
+        const int incl = wave_incl_scan(cnt), excl = incl - cnt, total = __builtin_amdgcn_readlane(incl, 63);
+        // lanes for the pairs of as many candidates at a time as 64 hold
+        for (int done = 0; done < total;) {
+            const bool take = cnt > 0 && excl >= done && incl <= done + 64;
+            const unsigned long long tm = wave_ballot(take);
+            const int upto = __builtin_amdgcn_readlane(incl, 63 - (int)__builtin_clzll(tm));
+            // this lane's pair: the candidate's lane (each candidate's lane
+            // number at its first pair, then the largest so far), and its place
+            // among that one's pairs
+            l_own[lane] = 0;
+            if (take) l_own[excl - done] = lane;
+            wave_sync();
+            const int own = wave_incl_max(l_own[lane]);
+            wave_sync();
+            const bool pair = lane < upto - done;
+            const int first = __shfl(excl, own) - done, n = __shfl(cnt, own);
+            int rank = lane - first;
+            const int cc = __shfl(c, own), pcx = __shfl(cx, own), pcy = __shfl(cy, own);
+            uint32_t b = 0;
+            int qq = 0;
+            bool found = false;
+#pragma unroll
+            for (int i = 0; i < NW; ++i) {
+                const uint32_t v = (uint32_t)__shfl((int)w[i], own);
+                const int m = __popc(v);
+                if (!found && rank < m) {
+                    found = true;
+                    b = v;
+                    qq = 32 * i;
+                }
+                rank -= found ? 0 : m;
+            }
+            qq += nth_bit(b, rank);
+            const int qy = small_div(qq, kInvSide);
+            const int kx = pcx - D + (qq - __mul24(qy, SIDE)), ky = pcy - D + qy;
+            const int kc = pair ? __mul24(ky, RW) + kx : 0;
+            float p = 0.0f;
+            float oj[3], dzj[3];
+            if (pair) {
+                const int64_t pj = (int64_t)(y0 + pcy) * g.w + (x0 + pcx);
+                float nzj[3], wv[3], v[kRecvFloats<LT>];
+                ld3(occ.dz, pj, dzj);
+                ld3(occ.nz, pj, nzj);
+                for (int a = 0; a < 3; ++a) oj[a] = s_o[a * CELLS + cc];
+                const float ok[3] = {s_o[kc], s_o[CELLS + kc], s_o[2 * CELLS + kc]};
+                const float nk[3] = {s_n[kc], s_n[CELLS + kc], s_n[2 * CELLS + kc]};
+                rel_vec(oj, ok, dzj, wv);
+                for (int a = 0; a < kRecvFloats<LT>; ++a) v[a] = s_sh[a * CELLS + kc];
+                p = dens_light(wv, nk, recv_load(v, L), nzj, L);
+            }
+            // targets: pixels of the tile within R of the candidate
+            const bool target = pair && p > 0.0f && (uint32_t)(kx - R) < (uint32_t)TX && (uint32_t)(ky - R) < (uint32_t)TY &&
+                                abs(kx - pcx) <= R && abs(ky - pcy) <= R;
+            if (wave_ballot(target) != 0ull) {
+                const int at = (ky << 8) | kx;
+                float P = 0.0f, h = 0.0f;
+                int last = -1;
+                // (four pairs' values read ahead of their sums; every lane
+                // takes part, those with fewer pairs read their last one)
+                for (int m0 = 0; wave_ballot(target && m0 < n) != 0ull; m0 += 4) {
+                    int am[4];
+                    float pm[4];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const int src = first + min(m0 + e, n - 1);
+                        am[e] = __shfl(at, src);
+                        pm[e] = __shfl(p, src);
+                    }
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        if (m0 + e < n) {
+                            const int ym = am[e] >> 8, xm = am[e] & 255;
+                            if (ym != last) {
+                                P += h;
+                                h = 0.0f;
+                                last = ym;
+                            }
+                            if (abs(ym - ky) <= R && abs(xm - kx) <= R) h += pm[e];
+                        }
+                    }
+                }
+                P += h;
+                if (target) {
+                    float term = p * __builtin_amdgcn_rcpf(P);
+                    if constexpr (MODE >= kShadowSA || kBilinear<LT>)
+                        term = weighted_term<MODE>(term, s_o, s_n, s_sh, CELLS, kc, oj, dzj, L);
+                    atomicAdd(&s_B[(ky - R) * TX + (kx - R)], (unsigned long long)rintf(term * 4294967296.0f));
+                }
+            }
+            done = upto;
+        }
+    }
+}
+
+// All candidates of a staged tile, row-task radii.
+template <int MODE, bool UNB, class LT, int R>
+__device__ inline void tile_candidates(const WinLayout &lay, unsigned char *smem, const GBufView &g,
+                                       const OccView &occ, float R2, const LT &L,
+                                       const uint32_t *__restrict__ bits, int words, int tx, int ty) {
+    int *s_count = reinterpret_cast<int *>(smem + lay.list_off);
+    const uint16_t *s_list = reinterpret_cast<const uint16_t *>(smem + lay.list_off + kListHead * sizeof(int));
+    if constexpr (kPairBody<MODE, UNB, LT>) {
+        tile_pair_candidates<MODE, UNB, LT, R>(lay, smem, g, occ, L, bits, words, tx, ty);
+        __syncthreads();
+        if (s_count[3] > 0)
+            tile_row_candidates<MODE, UNB, LT, R>(lay, smem, g, occ, R2, L, bits, words, tx, ty,
+                                                  reinterpret_cast<const uint16_t *>(smem + lay.many_off), &s_count[3],
+                                                  &s_count[4]);
+    } else {
+        tile_row_candidates<MODE, UNB, LT, R>(lay, smem, g, occ, R2, L, bits, words, tx, ty, s_list, &s_count[0],
+                                              &s_count[1]);
+    }
+}
+
 // One kWTX x kWTY target tile (tx, ty) of the sliding-window estimator; every
 // thread of the block calls it.  `smem` holds win_layout(R, ...).total bytes.
 template <int MODE, bool UNB, class LT = LightF>
@@ -339,7 +580,8 @@ __device__ inline void reuse_window_tile(unsigned char *smem, const GBufView &g,
                                          const LT &L, const uint32_t *__restrict__ bits, int words, int R,
                                          int dark_guard, int accumulate, float *out, int tx, int ty,
                                          float scale = 1.0f) {
-    const WinLayout lay = win_layout(R, MODE, UNB, words, kRecvFloats<LT>);
+    const int block = blockDim.x;
+    const WinLayout lay = win_layout(R, MODE, kPairBody<MODE, UNB, LT>, words, kRecvFloats<LT>, block >> 6);
     const int TX = kWTX, TY = kWTY, RW = lay.RWX, CELLS = lay.cells, D = 2 * R, SIDE = lay.side, TW = 2 * R + 1;
     const float inv_rw = 1.0f / (float)RW;
     unsigned long long *s_B = reinterpret_cast<unsigned long long *>(smem + lay.B_off);
@@ -349,20 +591,21 @@ __device__ inline void reuse_window_tile(unsigned char *smem, const GBufView &g,
     uint8_t *s_valid = smem + lay.valid_off;
     uint8_t *s_miss = smem + lay.miss_off;
     int *s_count = reinterpret_cast<int *>(smem + lay.list_off);
-    uint16_t *s_list = reinterpret_cast<uint16_t *>(smem + lay.list_off + 4 * sizeof(int));
+    uint16_t *s_list = reinterpret_cast<uint16_t *>(smem + lay.list_off + kListHead * sizeof(int));
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     float *w_dens = reinterpret_cast<float *>(smem + lay.wave_off) + wave * (lay.dens + lay.hsum);
     float *w_h = w_dens + lay.dens;
 
     const int x0 = tx * TX - R, y0 = ty * TY - R;
     const int tid = threadIdx.x;
-    if (tid == 0) s_count[0] = s_count[1] = 0;
-    for (int t = tid; t < TX * TY; t += kRBlock) s_B[t] = 0ull;
+    if (tid < kListHead) s_count[tid] = 0;
+    for (int t = tid; t < TX * TY; t += block) s_B[t] = 0ull;
     __syncthreads();
 
     // Stage receivers (o, n, shadow terms), validity, misses, validation
     // bits, and compact the cells whose ray found an occluder.
-    for (int c = tid; c < CELLS; c += kRBlock) {
+    float qmax = 0.0f;
+    for (int c = tid; c < CELLS; c += block) {
         const int cyy = small_div(c, inv_rw);
         int gx = x0 + (c - __mul24(cyy, RW)), gy = y0 + cyy;
         bool inside = gx >= 0 && gx < g.w && gy >= 0 && gy < g.h;
@@ -386,23 +629,29 @@ __device__ inline void reuse_window_tile(unsigned char *smem, const GBufView &g,
             float v[kRecvFloats<LT>] = {};
             if (valid) recv_store(recv_of(o, L), v);
             for (int a = 0; a < kRecvFloats<LT>; ++a) s_sh[a * CELLS + c] = v[a];
+            if (kPairBody<MODE, UNB, LT> && !UNB && valid) qmax = fmaxf(qmax, recv_size(o, L));
         }
         s_valid[c] = valid;
         s_miss[c] = valid && hit == OCR_HIT_MISS;
         if (valid && hit < OCR_HIT_SELF) s_list[atomicAdd(s_count, 1)] = (uint16_t)c;
     }
+    if (kPairBody<MODE, UNB, LT> && !UNB && row_body_radius(R)) {
+        // (floats from 0 up order as integers)
+        const int m = ~wave_min_i(~__float_as_int(qmax));
+        if (lane == 0) atomicMax(&s_count[2], m);
+    }
     __syncthreads();
 
     if (R == 1) {
-        tile_row_candidates<MODE, UNB, LT, 1>(lay, smem, g, occ, R2, L, bits, words, tx, ty);
+        tile_candidates<MODE, UNB, LT, 1>(lay, smem, g, occ, R2, L, bits, words, tx, ty);
     } else if (R == 2) {
-        tile_row_candidates<MODE, UNB, LT, 2>(lay, smem, g, occ, R2, L, bits, words, tx, ty);
+        tile_candidates<MODE, UNB, LT, 2>(lay, smem, g, occ, R2, L, bits, words, tx, ty);
     } else if (R == 3) {
-        tile_row_candidates<MODE, UNB, LT, 3>(lay, smem, g, occ, R2, L, bits, words, tx, ty);
+        tile_candidates<MODE, UNB, LT, 3>(lay, smem, g, occ, R2, L, bits, words, tx, ty);
     } else {
         // Other radii: one wave per candidate j.
         const int ncand = *s_count;
-        for (int li = wave; li < ncand; li += kRBlock / 64) {
+        for (int li = wave; li < ncand; li += block >> 6) {
             const int c = __builtin_amdgcn_readfirstlane((int)s_list[li]);
             const int cy = small_div(c, inv_rw), cx = c - __mul24(cy, RW);
             const int64_t gj = (int64_t)(y0 + cy) * g.w + (x0 + cx);
@@ -557,7 +806,7 @@ __device__ inline void reuse_window_tile(unsigned char *smem, const GBufView &g,
     __syncthreads();
 
     // one lane per target
-    for (int t = tid; t < TX * TY; t += kRBlock) {
+    for (int t = tid; t < TX * TY; t += block) {
         const int ix = t % TX, iy = t / TX;
         const int px = tx * TX + ix, py = ty * TY + iy;
         if (px >= g.w || py >= g.h) continue;

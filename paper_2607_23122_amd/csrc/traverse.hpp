@@ -402,33 +402,6 @@ __device__ inline float uniform_f(float v) {
     return __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, v)));
 }
 
-// Minimum / maximum over the wave as a scalar.  The floats are compared as
-// integers that order alike (negative ones with their lower bits flipped; a NaN
-// lies beyond the infinities), since an integer min or max takes the other
-// lane's value as a DPP operand of its own: six instructions, four steps
-// within the rows of 16 lanes and two across them, where a shuffle and a float
-// min per step take two and an LDS access.  Lane 63 holds the result.
-__device__ inline int ordered_int(float v) {
-    const int i = __builtin_bit_cast(int, v);
-    return i ^ ((i >> 31) & 0x7FFFFFFF);
-}
-template <int CTRL>
-__device__ inline int dpp_min(int v) {
-    return min(v, __builtin_amdgcn_update_dpp(0x7FFFFFFF, v, CTRL, 0xF, 0xF, false));
-}
-__device__ inline float from_ordered(int i) { return __builtin_bit_cast(float, i ^ ((i >> 31) & 0x7FFFFFFF)); }
-__device__ inline int wave_min_i(int v) {
-    v = dpp_min<0x111>(v);  // row_shr:1, 2, 4, 8
-    v = dpp_min<0x112>(v);
-    v = dpp_min<0x114>(v);
-    v = dpp_min<0x118>(v);
-    v = dpp_min<0x142>(v);  // row_bcast:15, 31
-    v = dpp_min<0x143>(v);
-    return __builtin_amdgcn_readlane(v, 63);
-}
-__device__ inline float wave_min_u(float f) { return from_ordered(wave_min_i(ordered_int(f))); }
-__device__ inline float wave_max_u(float f) { return -wave_min_u(-f); }
-
 // Where walks of segments inside the wave-uniform box [ulo, uhi] may start.
 // The box, padded, is U; from the root the descent goes on while exactly one
 // child box of the node overlaps U and that child is not a leaf.  A triangle
