@@ -225,17 +225,10 @@ __device__ inline bool may_support(const CandTerms &c, float hk, float ak, float
     const float A = __fmaf_rn(c.H, ak, c.U * hk), B = __fmaf_rn(c.H, bk, c.V * hk);
     return fmaxf(fabsf(A), fabsf(B)) <= __fmaf_rn(0.5001f, fabsf(c.H + hk), c.slack);
 }
-// term_size of a receiver (the largest over the lights)
+// term_size of a receiver
 __device__ inline float recv_size(const float o[3], const LightF &L) {
     const RecvShadow r = recv_shadow(o, L);
     return term_size(r.hk, r.ak, r.bk, light_scale(L));
-}
-__device__ inline float recv_size(const float o[3], const LightSetF &S) {
-    float q = 0.0f;
-#pragma unroll
-    for (int l = 0; l < kMaxLights; ++l)
-        if (l < S.n) q = fmaxf(q, recv_size(o, S.l[l]));
-    return q;
 }
 
 // Floats of a receiver's light terms in LDS.
@@ -291,39 +284,16 @@ __device__ inline float dens_light(const float w[3], const float nk[3], const Re
     return p;
 }
 
-// The terms of a candidate staged in cell c (sh: the staged light terms, or
-// points for several lights, `cells` apart per component) ...
-__device__ inline void cell_terms(const float *sh, int cells, int c, const float dzj[3], const LightF &L, float qmax,
-                                  CandTerms (&t)[1]) {
-    t[0] = cand_terms(RecvShadow{sh[c], sh[cells + c], sh[2 * cells + c]}, dzj, L, qmax);
+// The terms of a candidate staged in cell c (sh: the staged light terms, `cells`
+// apart per component) ...
+__device__ inline CandTerms cell_terms(const float *sh, int cells, int c, const float dzj[3], const LightF &L,
+                                       float qmax) {
+    return cand_terms(RecvShadow{sh[c], sh[cells + c], sh[2 * cells + c]}, dzj, L, qmax);
 }
-__device__ inline void cell_terms(const float *sh, int cells, int c, const float dzj[3], const LightSetF &S,
-                                  float qmax, CandTerms (&t)[kMaxLights]) {
-    const float oj[3] = {sh[c], sh[cells + c], sh[2 * cells + c]};
-#pragma unroll
-    for (int l = 0; l < kMaxLights; ++l)
-        if (l < S.n) t[l] = cand_terms(recv_shadow(oj, S.l[l]), dzj, S.l[l], qmax);
+// ... and whether the receiver staged in cell k may have a positive density of it.
+__device__ inline bool cell_support(const float *sh, int cells, int k, const CandTerms &t) {
+    return may_support(t, sh[k], sh[cells + k], sh[2 * cells + k]);
 }
-// ... and whether the receiver staged in cell k may have a positive density of
-// it (of any light).
-__device__ inline bool cell_support(const float *sh, int cells, int k, const LightF &, const CandTerms (&t)[1]) {
-    return may_support(t[0], sh[k], sh[cells + k], sh[2 * cells + k]);
-}
-__device__ inline bool cell_support(const float *sh, int cells, int k, const LightSetF &S,
-                                    const CandTerms (&t)[kMaxLights]) {
-    const float ok[3] = {sh[k], sh[cells + k], sh[2 * cells + k]};
-    bool any = false;
-#pragma unroll
-    for (int l = 0; l < kMaxLights; ++l) {
-        if (l < S.n) {
-            const RecvShadow r = recv_shadow(ok, S.l[l]);
-            any |= may_support(t[l], r.hk, r.ak, r.bk);
-        }
-    }
-    return any;
-}
-template <class LT>
-constexpr int kLightTerms = std::is_same<LT, LightSetF>::value ? kMaxLights : 1;
 
 __device__ inline float front_light(const float o[3], const float n[3], const LightF &L) {
     return front_fraction(o, n, L);

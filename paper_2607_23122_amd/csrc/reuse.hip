@@ -233,7 +233,7 @@ static hipError_t launch_win(const GBufView &g, const OccView &occ, float R2, co
     int tiles_x = (g.w + kWTX - 1) / kWTX, tiles_y = (g.h + kWTY - 1) / kWTY;
     int nt = tiles_x * tiles_y;
     // (row-task radii; the others' per-wave scratch would take the LDS)
-    const int lanes = nt <= kFewTiles && row_body_radius(p.radius) ? kWinMost : kRBlock;
+    const int lanes = kWideTile<MODE, UNB, LT> && nt <= kFewTiles && row_body_radius(p.radius) ? kWinMost : kRBlock;
     WinLayout lay = win_layout(p.radius, MODE, kPairBody<MODE, UNB, LT>, words, kRecvFloats<LT>, lanes / 64);
     // dynamic-LDS limit raised so far (64 KB by default); several host
     // threads may launch at once

@@ -44,6 +44,12 @@ __host__ __device__ constexpr int few_pairs(int R) { return 4 * R; }
 // lights biased at 1080p 0.50 ms by row tasks, 0.58 by pairs).
 template <int MODE, bool UNB, class LT>
 constexpr bool kPairBody = MODE != OCR_AO && (UNB || !std::is_same<LT, LightSetF>::value);
+// Whether a window tile's block may have kWinMost lanes.  Several lights' row tasks
+// keep kRBlock, a constant: with a run-time size their kernel, short of scalar
+// registers, reads the lights' constants again in the loops (two lights biased at
+// 1080p 519 us with it, 499 without).
+template <int MODE, bool UNB, class LT>
+constexpr bool kWideTile = MODE == OCR_AO || kPairBody<MODE, UNB, LT>;
 // Counters ahead of the candidate list: candidates, cursor, largest term_size
 // (as its bits), candidates left to the row tasks, their cursor.
 constexpr int kListHead = 8;
@@ -311,7 +317,7 @@ __device__ inline void tile_row_candidates(const WinLayout &lay, unsigned char *
                         float v[kRecvFloats<LT>];
                         for (int a = 0; a < kRecvFloats<LT>; ++a) v[a] = s_sh[a * CELLS + kc];
                         const float d = dens_light(w, nk, recv_load(v, L), nzj, L);
-                        p[e] = on ? d : 0.0f;
+                        p[e] = !kPairBody<MODE, UNB, LT> || on ? d : 0.0f;
                     }
                 }
             }
@@ -407,8 +413,7 @@ __device__ inline void tile_pair_candidates(const WinLayout &lay, unsigned char 
             for (int i = 0; i < NW; ++i) w[i] = 0u;
             float dzj[3];
             ld3(occ.dz, gj, dzj);
-            CandTerms t[kLightTerms<LT>];
-            cell_terms(s_sh, CELLS, c, dzj, L, qmax, t);
+            const CandTerms t = cell_terms(s_sh, CELLS, c, dzj, L, qmax);
 #pragma unroll 1
             for (int y = 0; y < SIDE; ++y) {
                 // (a row outside the staged cells is read from the nearest one
@@ -416,7 +421,7 @@ __device__ inline void tile_pair_candidates(const WinLayout &lay, unsigned char 
                 const int k0 = __mul24(min(max(cy - D + y, 0), RH - 1), RW) + (cx - D);
                 uint32_t m = 0;
 #pragma unroll
-                for (int e = 0; e < SIDE; ++e) m |= cell_support(s_sh, CELLS, k0 + e, L, t) ? 1u << e : 0u;
+                for (int e = 0; e < SIDE; ++e) m |= cell_support(s_sh, CELLS, k0 + e, t) ? 1u << e : 0u;
                 // the row's bits enter above the earlier ones
 #pragma unroll
                 for (int i = 0; i < NW - 1; ++i) w[i] = __builtin_amdgcn_alignbit(w[i + 1], w[i], SIDE);
@@ -580,7 +585,7 @@ __device__ inline void reuse_window_tile(unsigned char *smem, const GBufView &g,
                                          const LT &L, const uint32_t *__restrict__ bits, int words, int R,
                                          int dark_guard, int accumulate, float *out, int tx, int ty,
                                          float scale = 1.0f) {
-    const int block = blockDim.x;
+    const int block = kWideTile<MODE, UNB, LT> ? (int)blockDim.x : kRBlock;
     const WinLayout lay = win_layout(R, MODE, kPairBody<MODE, UNB, LT>, words, kRecvFloats<LT>, block >> 6);
     const int TX = kWTX, TY = kWTY, RW = lay.RWX, CELLS = lay.cells, D = 2 * R, SIDE = lay.side, TW = 2 * R + 1;
     const float inv_rw = 1.0f / (float)RW;
@@ -629,7 +634,9 @@ __device__ inline void reuse_window_tile(unsigned char *smem, const GBufView &g,
             float v[kRecvFloats<LT>] = {};
             if (valid) recv_store(recv_of(o, L), v);
             for (int a = 0; a < kRecvFloats<LT>; ++a) s_sh[a * CELLS + c] = v[a];
-            if (kPairBody<MODE, UNB, LT> && !UNB && valid) qmax = fmaxf(qmax, recv_size(o, L));
+            if constexpr (kPairBody<MODE, UNB, LT> && !UNB) {
+                if (valid) qmax = fmaxf(qmax, recv_size(o, L));
+            }
         }
         s_valid[c] = valid;
         s_miss[c] = valid && hit == OCR_HIT_MISS;
