@@ -17,8 +17,8 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libocr.so")
-SOURCES = ["api.cpp", "bvh_build.cpp", "trace.hip", "shaft.hip", "reuse.hip", "baselines.hip", "batch.hip", "plan.cpp",
-           "server.cpp", "scratch.hip"]
+SOURCES = ["api.cpp", "bvh_build.cpp", "trace.hip", "shaft.hip", "validate_light.hip", "reuse.hip", "baselines.hip",
+           "batch.hip", "plan.cpp", "server.cpp", "scratch.hip"]
 ARCH = "gfx950"
 
 

@@ -159,7 +159,7 @@ __global__ __launch_bounds__(kBlock) void trace_count_kernel(DeviceBVH bvh, GBuf
 constexpr int kCompactTiles = 4;  // tiles per compaction block
 
 __global__ __launch_bounds__(kBlock) void clear_count_kernel(uint32_t *lists) {
-    if (threadIdx.x < 8) lists[threadIdx.x * kCountStride] = 0u;
+    if (threadIdx.x < 16) lists[(threadIdx.x >> 1) * kCountStride + (threadIdx.x & 1)] = 0u;
 }
 
 // Blocks: 8 * ceil(ceil(ntiles / 8) / kCompactTiles).
@@ -571,6 +571,10 @@ static hipError_t launch_validate_t(const DeviceBVH &bvh, const GBufView &g, con
     uint32_t *lists = bits + (size_t)g.w * g.h * words;
     const uint32_t per_xcd = (uint32_t)((nt + 7) / 8) * (uint32_t)kBlock;
     hipLaunchKernelGGL(clear_count_kernel, dim3(1), dim3(kBlock), 0, st, lists);
+    // the light effects' windows up to radius 3 by marks (a mask of (4r + 1)^2 bits
+    // in registers); figures of both in validate_light.hip
+    if (p.pattern == OCR_WINDOW && mode != OCR_AO && !stats && p.radius >= 1 && p.radius <= 3)
+        return launch_validate_light(bvh, g, occ, L, p.radius, bits, lists, per_xcd, st);
     const int per_band = (nt + 7) / 8;
     hipLaunchKernelGGL(compact_kernel, dim3(8 * ((per_band + kCompactTiles - 1) / kCompactTiles)), dim3(kBlock), 0, st,
                        g, occ, lists, per_xcd, tiles_x, nt);

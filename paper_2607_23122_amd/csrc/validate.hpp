@@ -2,6 +2,7 @@
 // candidate lists, a pair's receiver and the run bookkeeping.
 #pragma once
 #include "density.hpp"
+#include "lights.hpp"
 #include "ocr_common.hpp"
 #include "trace_pixel.hpp"
 
@@ -62,5 +63,12 @@ struct RunCand {
 // shaft.hip: the validation of AO windows
 hipError_t launch_validate_shaft(const DeviceBVH &bvh, const GBufView &g, const OccView &occ, float R, int D, int words,
                                  uint32_t *bits, const uint32_t *lists, uint32_t per_xcd, hipStream_t st);
+
+// validate_light.hip: the validation of the light effects' windows of radius 1
+// to 3; the candidates it leaves are appended to the lists
+hipError_t launch_validate_light(const DeviceBVH &bvh, const GBufView &g, const OccView &occ, const LightF &L, int radius,
+                                 uint32_t *bits, uint32_t *lists, uint32_t per_xcd, hipStream_t st);
+hipError_t launch_validate_light(const DeviceBVH &bvh, const GBufView &g, const OccView &occ, const LightSetF &L, int radius,
+                                 uint32_t *bits, uint32_t *lists, uint32_t per_xcd, hipStream_t st);
 
 }  // namespace ocr

@@ -1,7 +1,8 @@
-"""The window reuse of one light's records pair by pair against the row tasks,
-which a list of one light takes: the same estimates, for lights that mark few
-and many receivers of a candidate, near and far, turned and oblong, in frames
-with cut tiles and pixels without a surface."""
+"""The light effects' pairs found from marks, against what evaluates every
+density: the window reuse against the row tasks, which a list of one light
+takes, and the validation bits against the work-counting walk; for lights that
+mark few and many receivers of a candidate, near and far, turned and oblong, in
+frames with cut tiles and pixels without a surface."""
 import numpy as np
 import pytest
 
@@ -19,18 +20,23 @@ LIGHTS = {
 }
 
 
-# (333 x 197 runs eight waves to a tile, 1367 x 771 four)
-@pytest.mark.parametrize("size", [(333, 197), (1367, 771)])
-@pytest.mark.parametrize("light", sorted(LIGHTS))
-def test_pairs_equal_row_tasks(light, size):
-    import torch
-    import paper_2607_23122_amd as ocr
+def _frame(light, size):
     scene = w.boxes_scene(1)
     gb = w.render_gbuffer(scene, w.boxes_camera(*size))
     c, eu, ev = (np.array(v, np.float32) for v in LIGHTS[light])
     lt = w.RectLight(c, eu, ev)
     if np.cross(eu, ev)[1] > 0:  # (emitting upwards)
         lt = w.RectLight(c, ev, eu)
+    return scene, gb, lt
+
+
+# (333 x 197 runs eight waves to a tile, 1367 x 771 four)
+@pytest.mark.parametrize("size", [(333, 197), (1367, 771)])
+@pytest.mark.parametrize("light", sorted(LIGHTS))
+def test_pairs_equal_row_tasks(light, size):
+    import torch
+    import paper_2607_23122_amd as ocr
+    scene, gb, lt = _frame(light, size)
     bvh = ocr.build_bvh(scene.V, scene.F)
     dg = ocr.DeviceGBuffer.from_host(gb)
     occ = ocr.trace_occluders(bvh, dg, "shadow", 1.0, lt, 5, 0)
@@ -45,3 +51,29 @@ def test_pairs_equal_row_tasks(light, size):
         # of the one light's (a product and a division: two roundings of a number
         # up to 1)
         assert np.abs(a - b).max() <= 2.0 ** -22
+
+
+@pytest.mark.parametrize("size", [(61, 37), (333, 197)])
+@pytest.mark.parametrize("light", sorted(LIGHTS))
+def test_marked_bits_equal_counted(light, size):
+    import torch
+    import paper_2607_23122_amd as ocr
+    scene, gb, lt = _frame(light, size)
+    bvh = ocr.build_bvh(scene.V, scene.F)
+    dg = ocr.DeviceGBuffer.from_host(gb)
+    occ = ocr.trace_occluders(bvh, dg, "shadow", 1.0, lt, 5, 0)
+    n = size[0] * size[1]
+    for radius in (1, 2, 3):
+        log(f"[pairs] bits {light} {size} window {radius}")
+        p = ocr.reuse_params("window", radius, 8, "unbiased")
+        words = ((4 * radius + 1) ** 2 + 31) // 32
+        bits = []
+        # one light, a list of it (and of it twice), the counting walk
+        for lights, stats in ((lt, None), ([lt], None), ([lt, lt], None), (lt, torch.zeros(5, dtype=torch.int64, device="cuda"))):
+            ws = torch.zeros(ocr.workspace_bytes(gb.width, gb.height, p), dtype=torch.uint8, device="cuda")
+            ocr.validate_pairs(bvh, dg, occ, "shadow", 1.0, lights, p, ws, stats=stats)
+            bits.append(ws.cpu().numpy()[:4 * n * words].view(np.uint32).reshape(n, words))
+        cand = (occ.hit_u32() < 0xFFFFFFFE).ravel()
+        assert cand.any()
+        for b in bits[:-1]:
+            assert np.array_equal(b[cand], bits[-1][cand])
