@@ -112,12 +112,8 @@ __global__ __launch_bounds__(kBBlock2) void light_reuse_kernel(DeviceBVH bvh, GB
                 }
             }
             if (wave_ballot(overflow) != 0ull) {
-                const TRay rr[1] = {ray};
-                const bool wr[1] = {overflow};
-                bool br[1];
-                WalkStats st;
-                traverse_wave_any<1>(bvh, rr, 1.0f, wr, br, wstack[threadIdx.x >> 6], st);
-                if (overflow) blocked = br[0];
+                const bool hit = traverse_wave_any(bvh, ray, 1.0f, overflow, wstack[threadIdx.x >> 6]);
+                if (overflow) blocked = hit;
             }
             if (want && !blocked) ++vis;
         }

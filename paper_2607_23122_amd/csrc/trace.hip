@@ -335,11 +335,7 @@ __global__ __launch_bounds__(kBlock, 7) void validate_window_kernel(DeviceBVH bv
                 if (COUNT) {
                     blocked = traverse_wave_any_masked(bvh, r, 1.0f - 1e-4f, want, wnode[wave], wmask[wave], ws);
                 } else {
-                    TRay rr[1] = {r};
-                    const bool wr[1] = {want};
-                    bool br[1];
-                    traverse_wave_any<1>(bvh, rr, 1.0f - 1e-4f, wr, br, wnode[wave], ws, entry);
-                    blocked = br[0];
+                    blocked = traverse_wave_any(bvh, r, 1.0f - 1e-4f, want, wnode[wave], entry);
                 }
                 if (want && !blocked) atomicOr(&wbits[wave][b * words + (q >> 5)], 1u << (q & 31));
             }

@@ -319,19 +319,15 @@ __global__ __launch_bounds__(kLBlock, 7) void walk_marked_kernel(DeviceBVH bvh, 
             wave_sync();
         }
         for (int e0 = 0; e0 < count; e0 += 64) {
-            TRay rr[1];
-            rr[0].ign0 = rr[0].ign1 = OCR_HIT_MISS;
-            bool wr[1], br[1];
+            TRay ray;
+            ray.ign0 = ray.ign1 = OCR_HIT_MISS;
             int own, q;
-            {
-                uint32_t primk;
-                float ok[3], wv[3];
-                wr[0] = pair_of(e0 + lane, own, q, primk, ok, wv, sure);
-                if (wr[0]) make_ray(ok, wv, cands[own].hj, primk, 1.0f - 1e-4f, rr[0]);
-            }
-            WalkStats ws;
-            traverse_wave_any<1>(bvh, rr, 1.0f - 1e-4f, wr, br, s_stack[wave], ws, 0u);
-            if (wr[0] && !br[0]) atomicOr(&out[own * NW + (q >> 5)], 1u << (q & 31));
+            uint32_t primk;
+            float ok[3], wv[3];
+            const bool want = pair_of(e0 + lane, own, q, primk, ok, wv, sure);
+            if (want) make_ray(ok, wv, cands[own].hj, primk, 1.0f - 1e-4f, ray);
+            const bool blocked = traverse_wave_any(bvh, ray, 1.0f - 1e-4f, want, s_stack[wave]);
+            if (want && !blocked) atomicOr(&out[own * NW + (q >> 5)], 1u << (q & 31));
         }
         wave_sync();
         if (word) bits[at_word] = out[lane];
