@@ -138,7 +138,8 @@ SERVED_SCENES = [dict(seed=100 + i, cells=c, spheres=n)
 SERVED_SIZES = [(1280, 720), (1920, 1080), (2560, 1440)]
 
 
-TRACE_TU = ["density.hpp", "lights.hpp", "ocr_common.hpp", "trace.hip", "trace_pixel.hpp", "traverse.hpp"]
+TRACE_TU = ["density.hpp", "lights.hpp", "ocr_common.hpp", "shaft.hip", "trace.hip", "trace_pixel.hpp", "traverse.hpp",
+            "validate.hpp"]
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "ao_1080p_hbm_traffic.md")
 
 
@@ -463,10 +464,12 @@ def run_frame(args, workload=None, ctx=None, cpu_seconds=None, amortised_reps=0)
     val_tops = val_ops / (per["validate"] * 1e-3) / 1e12
     reuse_tops = hits * window_reuse_ops(r, mode, bilinear) / (per["reuse_biased"] * 1e-3) / 1e12
     if dominant == "validate":
-        # traversal and densities are VALU-bound: price the useful operations
+        # traversal and densities are VALU-bound: price the useful operations of
+        # the counted walk (AO windows decide most pairs on the matrix cores
+        # instead, the light effects leave out most densities)
         # one validation per light type (single-light kernels carry LightF)
         lt = "ocr::LightSetF" if mode == "shadow2" else "ocr::LightF"
-        kname = f"ocr::validate_window_kernel<{0 if mode == 'ao' else 1}, false, {lt}, false>"
+        kname = "ocr::validate_shaft_kernel" if mode == "ao" else f"ocr::walk_marked_kernel<{lt}, {r}, 6, 6>"
         traffic = measured_traffic(kname) if workload == "ao_1080p" else None
         roof = alu_roof(val_tops, traffic=traffic, kernel=kname)
     elif dominant in ("reuse_biased", "reuse_unbiased"):
@@ -535,7 +538,7 @@ def run_frame(args, workload=None, ctx=None, cpu_seconds=None, amortised_reps=0)
         counted_trace(ocr, torch, bvh, dg, tmode, R, light, cfg["sample_seed"], args.steps - 1), per["trace"],
         "trace_kernel")
     if workload == "ao_1080p":
-        result["trace_roofline"]["traffic"] = measured_traffic("ocr::trace_kernel<0, ocr::LightF>")
+        result["trace_roofline"]["traffic"] = measured_traffic("ocr::trace_kernel<0, ocr::LightF, false>")
     if amortised_reps > 0 and mode in ("ao", "shadow"):
         result["amortised_ms_per_spp"] = amortised(ocr, torch, bvh, dg, occ, tmode, R, light, cfg["sample_seed"],
                                                    (p_none, p_b, p_u), ws, out_n, amortised_reps)
