@@ -73,8 +73,8 @@ __device__ inline void tile_pixel(int packing, int tw, int th, int it, int lane,
 
 // One wave per trace item: the wave traces the item's tile_w x tile_h pixels
 // in (tile_w * tile_h / 64) passes of one ray per lane.  Bounded to 7 waves
-// per SIMD: with both effects' walks inlined it takes 82 registers (5 waves)
-// otherwise, measured 4% slower.
+// per SIMD: the sixteen-view plan measured 3.52 ms, at 6 and at 8 waves 3.62 and
+// 3.61.
 template <bool FAR>
 __global__ __launch_bounds__(kBBlock, 7) void batch_trace_kernel(const BatchView *__restrict__ views,
                                                               const uint32_t *__restrict__ t_first,
@@ -120,9 +120,8 @@ __global__ __launch_bounds__(kBBlock, 7) void batch_trace_kernel(const BatchView
 
 // One block per reuse item (a window target tile of a window or no-reuse view).
 // Bounded to 7 waves per SIMD: every mode's body is inlined, and the
-// heaviest (light effects) spill a few words at 72 registers, but the
-// sixteen-view plan measured 3% faster than at 6 waves (4.33 against 4.46 ms,
-// identical outputs; 8 waves 4.40 ms).
+// heaviest (light effects) spill a few words at 72 registers; the sixteen-view
+// plan measured 3.52 ms, the same as at 6 waves (8 waves 3.54 ms).
 __global__ __launch_bounds__(kRBlock, 7) void batch_reuse_kernel(const BatchView *__restrict__ views,
                                                               const uint32_t *__restrict__ r_first, int nviews,
                                                               const uint32_t *__restrict__ q_start, uint32_t *ctr) {

@@ -223,7 +223,8 @@ __device__ inline CandTerms cand_terms(const RecvShadow &rj, const float dzj[3],
 }
 __device__ inline bool may_support(const CandTerms &c, float hk, float ak, float bk) {
     const float A = __fmaf_rn(c.H, ak, c.U * hk), B = __fmaf_rn(c.H, bk, c.V * hk);
-    return fmaxf(fabsf(A), fabsf(B)) <= __fmaf_rn(0.5001f, fabsf(c.H + hk), c.slack);
+    // (true where nothing can be said: terms beyond the floats)
+    return !(fmaxf(fabsf(A), fabsf(B)) > __fmaf_rn(0.5001f, fabsf(c.H + hk), c.slack));
 }
 // term_size of a receiver
 __device__ inline float recv_size(const float o[3], const LightF &L) {
