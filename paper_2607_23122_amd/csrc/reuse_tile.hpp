@@ -647,7 +647,7 @@ __device__ inline void reuse_window_tile(unsigned char *smem, const GBufView &g,
             if (valid) recv_store(recv_of(o, L), v);
             for (int a = 0; a < kRecvFloats<LT>; ++a) s_sh[a * CELLS + c] = v[a];
             if constexpr (kPairBody<MODE, UNB, LT> && !UNB) {
-                if (valid) qmax = fmaxf(qmax, recv_size(o, L));
+                if (valid && row_body_radius(R)) qmax = fmaxf(qmax, recv_size(o, L));
             }
         }
         s_valid[c] = valid;
@@ -668,9 +668,9 @@ __device__ inline void reuse_window_tile(unsigned char *smem, const GBufView &g,
     } else if (R == 3) {
         tile_candidates<MODE, UNB, LT, 3>(lay, smem, g, occ, R2, L, bits, words, tx, ty);
     } else {
-        // Other radii: one wave per candidate j.
+        // Other radii: one wave per candidate j (kRBlock lanes, see the launch).
         const int ncand = *s_count;
-        for (int li = wave; li < ncand; li += block >> 6) {
+        for (int li = wave; li < ncand; li += kRBlock >> 6) {
             const int c = __builtin_amdgcn_readfirstlane((int)s_list[li]);
             const int cy = small_div(c, inv_rw), cx = c - __mul24(cy, RW);
             const int64_t gj = (int64_t)(y0 + cy) * g.w + (x0 + cx);
