@@ -38,6 +38,7 @@
 // issue (0.92 ms of it) and, at 4 waves per SIMD (128 registers, 10 KB of LDS),
 // by the latency of the gather's dependent loads.
 #include "ocr_common.hpp"
+#include "shaft_box.hpp"
 #include "traverse.hpp"
 #include "validate.hpp"
 
@@ -122,43 +123,6 @@ __device__ inline half8 make_row(float x, float y, float z, float c) {
 // fourth component.  Beyond +-30000 it decides alone (|n . w| < 256 * 6144).
 __device__ inline float row_const(float c, int e) {
     return __builtin_amdgcn_fmed3f(__builtin_amdgcn_ldexpf(c, e - 8), -30000.0f, 30000.0f);
-}
-
-// Interval shaft of a candidate: z + s w with w in [lo, hi] and s in [0, 1]
-// (wave-uniform).
-struct Shaft {
-    float lo[3], hi[3], rlo[3], rhi[3];  // the box of w and its reciprocals
-    float zlo[3], zhi[3];                // -z times the reciprocals
-    uint32_t below;                      // bit a: lo[a] < 0; bit 3 + a: hi[a] > 0
-};
-
-// Whether the box [bl, bh] meets the shaft: per axis some s has s hi >= bl - z
-// and s lo <= bh - z, each a bound on s; the shaft meets the box only if the
-// bounds of all axes leave an s in [0, 1].  Which side a bound is on is the
-// wave's, so it branches (the empty asm keeps the compiler from computing both
-// and selecting, two more instructions per bound).  The FMA's cancellation
-// moves a plane by 2^-23 |z|, which the shaft's padding covers.
-__device__ inline bool shaft_meets(const Shaft &S, const float bl[3], const float bh[3]) {
-    float s0 = 0.0f, s1 = 1.0f + 1e-5f;
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-        const float p = __fmaf_rn(bl[a], S.rhi[a], S.zhi[a]), q = __fmaf_rn(bh[a], S.rlo[a], S.zlo[a]);
-        if (S.below & (8u << a)) {
-            s0 = fmaxf(s0, p);
-            asm volatile("" : "+v"(s0));
-        } else {
-            s1 = fminf(s1, p + 1e-5f);
-            asm volatile("" : "+v"(s1));
-        }
-        if (S.below & (1u << a)) {
-            s0 = fmaxf(s0, q);
-            asm volatile("" : "+v"(s0));
-        } else {
-            s1 = fminf(s1, q + 1e-5f);
-            asm volatile("" : "+v"(s1));
-        }
-    }
-    return s0 <= s1;
 }
 
 __global__ __launch_bounds__(64, 4) void validate_shaft_kernel(DeviceBVH bvh, GBufView g, OccView occ, float R2, int D,
@@ -264,21 +228,9 @@ __global__ __launch_bounds__(64, 4) void validate_shaft_kernel(DeviceBVH bvh, GB
                     W = max3f(W, fabsf(S.lo[a]), fabsf(S.hi[a]));
                 }
                 // the shaft padded by the rounding of its coordinates
-                S.below = 0;
                 cz = uniform_f(cz + W);
                 W = uniform_f(W);
-                const float pad = 0x1p-20f * cz + 0x1p-18f * W;
-#pragma unroll
-                for (int a = 0; a < 3; ++a) {
-                    const float l = S.lo[a] - pad, h = S.hi[a] + pad;
-                    S.lo[a] = uniform_f(fabsf(l) < 1e-20f ? 1e-20f : l);
-                    S.hi[a] = uniform_f(fabsf(h) < 1e-20f ? 1e-20f : h);
-                    S.rlo[a] = uniform_f(__builtin_amdgcn_rcpf(S.lo[a]));
-                    S.rhi[a] = uniform_f(__builtin_amdgcn_rcpf(S.hi[a]));
-                    S.zlo[a] = uniform_f(-z[a] * S.rlo[a]);
-                    S.zhi[a] = uniform_f(-z[a] * S.rhi[a]);
-                    S.below |= (S.lo[a] < 0.0f ? 1u << a : 0u) | (S.hi[a] > 0.0f ? 8u << a : 0u);
-                }
+                shaft_set(S, z, cz, W, [](float v) { return __builtin_amdgcn_rcpf(v); }, uniform_f);
                 S.below = (uint32_t)__builtin_amdgcn_readfirstlane((int)S.below);
                 // (a row of the receivers' common triangle is no use: it is
                 // never hit)
