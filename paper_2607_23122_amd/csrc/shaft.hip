@@ -71,7 +71,7 @@ struct ShaftCand {
 
 struct ShaftLds {
     half8 rows[4][64];                 // 64 triangles' rows: three edges, plane
-    uint2 rays[kShaftRays][2];         // (w, 256) hi, (w, 0) lo
+    alignas(16) uint2 rays[kShaftRays][2];  // listed: w; in test: (w, 256) hi, (w, 0) lo
     uint16_t ray_q[kShaftRays];        // their receivers' offsets
     uint32_t stack[kShaftStack];
     uint32_t refs[kShaftRefs];         // first triangle | kLeafBit if a second follows
@@ -120,7 +120,7 @@ __device__ inline half8 make_row(float x, float y, float z, float c) {
 }
 
 // The constant of a row scaled by 2^e, for w scaled by 2^ew and the 256 of w's
-// fourth component.  Beyond +-30000 it decides alone (|n . w| < 256 * 6144).
+// fourth component.  Beyond +-30000 it decides alone (|n . w| < 256 * 1536).
 __device__ inline float row_const(float c, int e) {
     return __builtin_amdgcn_fmed3f(__builtin_amdgcn_ldexpf(c, e - 8), -30000.0f, 30000.0f);
 }
@@ -212,9 +212,6 @@ __global__ __launch_bounds__(64, 4) void validate_shaft_kernel(DeviceBVH bvh, GB
             uint32_t prim0 = OCR_HIT_MISS;               // the first one's receiver triangle
             bool same = true;                            // ... and whether all have it
             int clo[3], chi[3];                          // the least w and -w (per lane, as ordered integers)
-            // w (|w| <= R) is scaled by 2^ew to below 2^9
-            const int ew = 8 - __builtin_amdgcn_readfirstlane(__builtin_amdgcn_frexp_expf(R2)) / 2;
-            const float scale = __builtin_amdgcn_ldexpf(1.0f, 8 - ew);
 
             // The listed segments against all triangles their shaft meets.
             auto test = [&]() {
@@ -231,6 +228,18 @@ __global__ __launch_bounds__(64, 4) void validate_shaft_kernel(DeviceBVH bvh, GB
                 cz = uniform_f(cz + W);
                 W = uniform_f(W);
                 shaft_set(S, z, cz, W, [](float v) { return __builtin_amdgcn_rcpf(v); }, uniform_f);
+                // The segments as halves, scaled by 2^ew to components below
+                // 2^8.  The scale is their own (of R it would be far from theirs
+                // where R is meant as no limit, and every pair would pass).
+                const int ew = 8 - __builtin_amdgcn_readfirstlane(__builtin_amdgcn_frexp_expf(W));
+                const float scale = __builtin_amdgcn_ldexpf(1.0f, 8 - ew);
+                for (int i = lane; i < nray; i += 64) {
+                    const float4 w = *reinterpret_cast<const float4 *>(s.rays[i]);
+                    uint2 hi, lo;
+                    split4(__builtin_amdgcn_ldexpf(w.x, ew), __builtin_amdgcn_ldexpf(w.y, ew),
+                           __builtin_amdgcn_ldexpf(w.z, ew), 256.0f, hi, lo);
+                    *reinterpret_cast<uint4 *>(s.rays[i]) = make_uint4(hi.x, hi.y, lo.x, lo.y);
+                }
                 S.below = (uint32_t)__builtin_amdgcn_readfirstlane((int)S.below);
                 // (a row of the receivers' common triangle is no use: it is
                 // never hit)
@@ -475,12 +484,8 @@ __global__ __launch_bounds__(64, 4) void validate_shaft_kernel(DeviceBVH bvh, GB
                             clo[a] = min(clo[a], ~i);
                             chi[a] = min(chi[a], i);
                         }
-                        uint2 hi, lo;
-                        split4(__builtin_amdgcn_ldexpf(w[0], ew), __builtin_amdgcn_ldexpf(w[1], ew),
-                               __builtin_amdgcn_ldexpf(w[2], ew), 256.0f, hi, lo);
                         const int at = nray + rank_in(m);
-                        s.rays[at][0] = hi;
-                        s.rays[at][1] = lo;
+                        *reinterpret_cast<float4 *>(s.rays[at]) = make_float4(w[0], w[1], w[2], 0.0f);
                         s.ray_q[at] = (uint16_t)q;
                         // free until found blocked
                         atomicOr(&s.bits[b * words + (q >> 5)], 1u << (q & 31));

@@ -77,3 +77,18 @@ def _layers(axis, at, gap, tile=0.02):
 def test_far_level_sheets(ocr, axis, at, gap):
     V, F, gb = _layers(axis, at, gap)
     _compare(ocr, f"sheets on axis {axis} at {at}, gap {gap}", V, F, gb, 1.0, 3, blocked=0.005)
+
+
+# radii that mean no limit, up to ones whose square is not finite; segments from
+# millimetres to kilometres
+@pytest.mark.parametrize("scale,R", [(1.0, 1e6), (1.0, 3e19), (1000.0, 1e6), (1000.0, 3e19), (0.01, 3e38)])
+def test_radius_without_limit(ocr, scale, R):
+    rng = np.random.default_rng(7)
+    n = 300
+    tri = rng.uniform(-1.5, 1.5, (n, 1, 3)) + rng.normal(0, 0.1, (n, 3, 3))
+    tri[:, :, 1] = np.abs(tri[:, :, 1]) + 0.05
+    top = np.array([[[-40.0, 3, -40], [40, 3, -40], [0, 3, 60]]])
+    own = np.array([[[-9.0, 0, -9], [-9, 0, 20], [20, 0, -9]]])
+    V = (np.concatenate([tri, top, own]).reshape(-1, 3) * scale).astype(np.float32)
+    gb = w.plane_gbuffer(67, 45, 0.05 * scale, (-1.6 * scale, 0.0, -1.1 * scale), prim=n + 1)
+    _compare(ocr, f"scale {scale}", V, np.arange(len(V), dtype=np.uint32).reshape(-1, 3), gb, R, 3, blocked=0.02)
