@@ -3,6 +3,7 @@
 // work on the caller's stream; they allocate nothing and never synchronise.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -200,6 +201,22 @@ ocr_status host_build(const float *verts, int64_t nverts, const uint32_t *tris, 
     return OCR_OK;
 }
 
+// DeviceBVH::extent, of at most 4096 triangles evenly spaced in the array.
+float lower_quartile_extent(const float *verts, const uint32_t *tris, int64_t ntris) {
+    float ext[4096];
+    const int64_t n = std::min<int64_t>(ntris, 4096);
+    for (int64_t i = 0; i < n; ++i) {
+        const uint32_t *t = tris + 3 * (i * ntris / n);
+        ext[i] = 0.0f;
+        for (int a = 0; a < 3; ++a) {
+            const float x = verts[3 * (size_t)t[0] + a], y = verts[3 * (size_t)t[1] + a], z = verts[3 * (size_t)t[2] + a];
+            ext[i] = std::max(ext[i], std::max(x, std::max(y, z)) - std::min(x, std::min(y, z)));
+        }
+    }
+    std::nth_element(ext, ext + n / 4, ext + n);
+    return ext[n / 4];
+}
+
 }  // namespace
 
 extern "C" {
@@ -254,6 +271,7 @@ ocr_status ocr_build_bvh(const float *verts, int64_t nverts, const uint32_t *tri
     b->dev.nnodes = (int64_t)hb.nodes.size();
     b->dev.ntris = ntris;
     b->dev.depth = hb.depth;
+    b->dev.extent = lower_quartile_extent(verts, tris, ntris);
     b->info.ntris = ntris;
     b->info.nnodes = (int64_t)hb.nodes.size();
     b->info.depth = hb.depth;

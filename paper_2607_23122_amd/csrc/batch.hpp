@@ -33,7 +33,7 @@ constexpr int kQueueStride = 32;
 constexpr int kQueueWords = 16 * kQueueStride;
 
 hipError_t launch_batch_reset(uint32_t *ctr, hipStream_t st);
-// far: some AO view's hierarchy has more than kNearNodes nodes (trace_pixel's FAR)
+// far: some AO view takes far_walk (trace_pixel's FAR, for all of them)
 hipError_t launch_batch_trace(const BatchView *views, const uint32_t *t_first, const uint32_t *t_tiles_x, int nviews,
                               const uint32_t *q_start, uint32_t *ctr, int tile_w, int tile_h, int packing, bool far,
                               int grid, hipStream_t st);

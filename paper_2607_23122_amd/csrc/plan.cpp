@@ -39,7 +39,7 @@ struct ocr_plan {
     int64_t pixels = 0, trace_items = 0, reuse_items = 0;
     size_t reuse_lds = 0;
     int cus = 256, trace_bpc = 1, reuse_bpc = 1;
-    bool far = false;  // an AO view's hierarchy has more than kNearNodes nodes
+    bool far = false;  // an AO view takes far_walk
     ocr_plan_tuning tun{};
     int tuned = 0, candidates = 0, from_cache = 0;
     double tune_ms = 0.0, best_trace_ms = 0.0;
@@ -416,7 +416,7 @@ ocr_status ocr_plan_create(const ocr_view_desc *views, int32_t nviews, const ocr
     int dev_cus = 0;
     if (hipDeviceGetAttribute(&dev_cus, hipDeviceAttributeMultiprocessorCount, p->device) == hipSuccess && dev_cus > 0)
         p->cus = dev_cus;
-    for (const ocr_view_desc &d : p->desc) p->far |= d.mode == OCR_AO && d.bvh->dev.nnodes > kNearNodes;
+    for (const ocr_view_desc &d : p->desc) p->far |= d.mode == OCR_AO && far_walk(d.bvh->dev, d.ao_radius);
     p->trace_bpc = batch_trace_blocks_per_cu(p->far);
     if (p->reuse_items > 0) {
         p->reuse_bpc = batch_reuse_blocks_per_cu(std::max<size_t>(p->reuse_lds, 16));

@@ -510,7 +510,7 @@ hipError_t launch_trace(const DeviceBVH &bvh, const GBufView &g, int mode, float
     int tiles_x;
     int nt = ntiles_for(g, tiles_x);
     dim3 grid(4 * grid_for(nt)), block(64);
-    if (mode == OCR_AO && bvh.nnodes > kNearNodes)
+    if (mode == OCR_AO && far_walk(bvh, R))
         hipLaunchKernelGGL((trace_kernel<OCR_AO, LightF, true>), grid, block, 0, st, bvh, g, R, L, seed32, sample, out,
                            tiles_x, nt);
     else if (mode == OCR_AO)
@@ -549,7 +549,8 @@ hipError_t launch_trace_count(const DeviceBVH &bvh, const GBufView &g, int mode,
 //             49154 triangles 960x540 0.18 / 0.17
 //   small frames: 770 triangles 256x256 radius 2 0.037 / 0.044, 960x540 0.114 / 0.089;
 //             1152 triangles 320x180 radius 2 0.023 / 0.031
-static bool shaft_pays(const DeviceBVH &bvh, const GBufView &g, int radius) {
+static bool shaft_pays(const DeviceBVH &bvh, const GBufView &g, float R, int radius) {
+    if (long_rays(bvh, R)) return false;
     const int64_t px = (int64_t)g.w * g.h;
     if (radius <= 1) return radius == 1 && bvh.ntris >= 65536 && px <= 1 << 20;
     return bvh.ntris >= (radius == 2 ? 16384 : 4096) || px <= 1 << 17;
@@ -590,7 +591,7 @@ static hipError_t launch_validate_t(const DeviceBVH &bvh, const GBufView &g, con
         else OCR_VAL(M, false, G);      \
     } while (0)
     if (p.pattern == OCR_WINDOW) {
-        if (mode == OCR_AO && !stats && shaft_pays(bvh, g, p.radius))
+        if (mode == OCR_AO && !stats && shaft_pays(bvh, g, R, p.radius))
             return launch_validate_shaft(bvh, g, occ, R, D, words, bits, lists, per_xcd, st);
         if (mode == OCR_AO) OCR_VAL_M(OCR_AO, false);
         else OCR_VAL_M(OCR_SHADOW, false);

@@ -171,3 +171,42 @@ def tiles(W, H, n, size, seed=0, margin=8):
         y = int(rng.integers(margin, H - size - margin))
         out.append((x, y, x + size, y + size))
     return out
+
+
+# The leading fields of an ocr_bvh handle that the launches choose kernels by
+# (DeviceBVH in csrc/ocr_common.hpp): offset and ctypes type.
+_BVH_FIELDS = dict(nnodes=(16, "c_int64"), ntris=(24, "c_int64"), depth=(32, "c_int32"), extent=(36, "c_float"))
+
+
+def bvh_field(bvh, name):
+    """A handle's field (no kernel reads these; their values choose one)."""
+    import ctypes
+    at, kind = _BVH_FIELDS[name]
+    return getattr(ctypes, kind).from_address(bvh.h.value + at)
+
+
+class route:
+    """Within the block the handle's fields hold other values, so that a frame
+    takes a kernel that its scene would not choose."""
+
+    def __init__(self, bvh, **fields):
+        self.bvh, self.fields = bvh, fields
+
+    def __enter__(self):
+        info = self.bvh.info()  # the layout is as stated
+        assert all(bvh_field(self.bvh, k).value == getattr(info, k) for k in ("nnodes", "ntris", "depth"))
+        self.old = {k: bvh_field(self.bvh, k).value for k in self.fields}
+        for k, v in self.fields.items():
+            bvh_field(self.bvh, k).value = v
+
+    def __exit__(self, *exc):
+        for k, v in self.old.items():
+            bvh_field(self.bvh, k).value = v
+
+
+# AO rays nearest first or collecting; AO windows by shafts (to 2^20 pixels) or by
+# the walk.  (Neither depends on the handle's depth, and its counts bound no walk.)
+NEAR_FIRST = dict(nnodes=1 << 30)
+COLLECT = dict(extent=1e30)
+SHAFT = dict(ntris=1 << 26, extent=1e30)
+WALK = dict(extent=0.0)
