@@ -87,33 +87,37 @@ __device__ inline void make_ray(const float o[3], const float d[3], uint32_t ign
 // where the third is exactly zero: a rounded difference of two rounded products
 // that is not zero has the sign of the exact one).  Nearly every test ends here.
 struct TriEdges {
-    float A[3], B[3], C[3];        // corners relative to the origin
-    float Ax, Ay, Bx, By, Cx, Cy;  // sheared
+    float Ax, Ay, Bx, By, Cx, Cy;  // sheared corners
     float U, V, W;
 };
 __device__ inline bool tri_edges(const TRay &r, const float4 &v0, const float4 &v1, const float4 &v2, TriEdges &e) {
 #pragma clang fp contract(off)
     const float va[3] = {v0.x, v0.y, v0.z}, vb[3] = {v1.x, v1.y, v1.z}, vc[3] = {v2.x, v2.y, v2.z};
+    float A[3], B[3], C[3];  // relative to the origin
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
-        e.A[c] = va[c] - r.o[c];
-        e.B[c] = vb[c] - r.o[c];
-        e.C[c] = vc[c] - r.o[c];
+        A[c] = va[c] - r.o[c];
+        B[c] = vb[c] - r.o[c];
+        C[c] = vc[c] - r.o[c];
     }
-    e.Ax = __fmaf_rn(r.m0[2], e.A[2], __fmaf_rn(r.m0[1], e.A[1], r.m0[0] * e.A[0]));
-    e.Ay = __fmaf_rn(r.m1[2], e.A[2], __fmaf_rn(r.m1[1], e.A[1], r.m1[0] * e.A[0]));
-    e.Bx = __fmaf_rn(r.m0[2], e.B[2], __fmaf_rn(r.m0[1], e.B[1], r.m0[0] * e.B[0]));
-    e.By = __fmaf_rn(r.m1[2], e.B[2], __fmaf_rn(r.m1[1], e.B[1], r.m1[0] * e.B[0]));
-    e.Cx = __fmaf_rn(r.m0[2], e.C[2], __fmaf_rn(r.m0[1], e.C[1], r.m0[0] * e.C[0]));
-    e.Cy = __fmaf_rn(r.m1[2], e.C[2], __fmaf_rn(r.m1[1], e.C[1], r.m1[0] * e.C[0]));
+    e.Ax = __fmaf_rn(r.m0[2], A[2], __fmaf_rn(r.m0[1], A[1], r.m0[0] * A[0]));
+    e.Ay = __fmaf_rn(r.m1[2], A[2], __fmaf_rn(r.m1[1], A[1], r.m1[0] * A[0]));
+    e.Bx = __fmaf_rn(r.m0[2], B[2], __fmaf_rn(r.m0[1], B[1], r.m0[0] * B[0]));
+    e.By = __fmaf_rn(r.m1[2], B[2], __fmaf_rn(r.m1[1], B[1], r.m1[0] * B[0]));
+    e.Cx = __fmaf_rn(r.m0[2], C[2], __fmaf_rn(r.m0[1], C[1], r.m0[0] * C[0]));
+    e.Cy = __fmaf_rn(r.m1[2], C[2], __fmaf_rn(r.m1[1], C[1], r.m1[0] * C[0]));
     e.U = e.Cx * e.By - e.Cy * e.Bx;
     e.V = e.Ax * e.Cy - e.Ay * e.Cx;
     e.W = e.Bx * e.Ay - e.By * e.Ax;
     // (no short circuit: a branch costs more than the second test)
     return !((int)(fminf(fminf(e.U, e.V), e.W) < 0.0f) & (int)(fmaxf(fmaxf(e.U, e.V), e.W) > 0.0f));
 }
-// The second half: the ray parameter t (> 0) or -1.
-__device__ inline float tri_distance(const TRay &r, const TriEdges &e) {
+// The second half: the ray parameter t (> 0) or -1.  It forms the corners
+// relative to the origin again (the empty asm keeps the first half's from being
+// kept for it): nine registers less across its branch, with which the validation
+// kernels at the register bound spilled (2.5 us more per launch).
+__device__ inline float tri_distance(const TRay &r, const float4 &v0, const float4 &v1, const float4 &v2,
+                                     const TriEdges &e) {
 #pragma clang fp contract(off)
     float U = e.U, V = e.V, W = e.W;
     if (U == 0.0f || V == 0.0f || W == 0.0f) {
@@ -127,9 +131,11 @@ __device__ inline float tri_distance(const TRay &r, const TriEdges &e) {
     }
     float det = U + V + W;
     if (det == 0.0f) return -1.0f;
-    float Az = __fmaf_rn(r.m2[2], e.A[2], __fmaf_rn(r.m2[1], e.A[1], r.m2[0] * e.A[0]));
-    float Bz = __fmaf_rn(r.m2[2], e.B[2], __fmaf_rn(r.m2[1], e.B[1], r.m2[0] * e.B[0]));
-    float Cz = __fmaf_rn(r.m2[2], e.C[2], __fmaf_rn(r.m2[1], e.C[1], r.m2[0] * e.C[0]));
+    float o[3] = {r.o[0], r.o[1], r.o[2]};
+    asm volatile("" : "+v"(o[0]), "+v"(o[1]), "+v"(o[2]));
+    float Az = __fmaf_rn(r.m2[2], v0.z - o[2], __fmaf_rn(r.m2[1], v0.y - o[1], r.m2[0] * (v0.x - o[0])));
+    float Bz = __fmaf_rn(r.m2[2], v1.z - o[2], __fmaf_rn(r.m2[1], v1.y - o[1], r.m2[0] * (v1.x - o[0])));
+    float Cz = __fmaf_rn(r.m2[2], v2.z - o[2], __fmaf_rn(r.m2[1], v2.y - o[1], r.m2[0] * (v2.x - o[0])));
     float T = __fmaf_rn(W, Cz, __fmaf_rn(V, Bz, U * Az));
     float t = T / det;
     return t > 0.0f ? t : -1.0f;
@@ -138,7 +144,7 @@ __device__ inline float tri_distance(const TRay &r, const TriEdges &e) {
 // Watertight triangle test.  Returns the ray parameter t (> 0) or -1.
 __device__ inline float tri_hit(const TRay &r, const float4 &v0, const float4 &v1, const float4 &v2) {
     TriEdges e;
-    return tri_edges(r, v0, v1, v2, e) ? tri_distance(r, e) : -1.0f;
+    return tri_edges(r, v0, v1, v2, e) ? tri_distance(r, v0, v1, v2, e) : -1.0f;
 }
 
 // Work of BVH walks: walks, node visits, box tests and triangle tests (a
@@ -362,7 +368,7 @@ __device__ inline Hit traverse_collect(const DeviceBVH &bvh, const float o[3], c
             const uint32_t id = __float_as_uint(v0.w);
             TriEdges e;
             if (tri_edges(r, v0, v1, v2, e) && id != ign0) {
-                const float t = tri_distance(r, e);
+                const float t = tri_distance(r, v0, v1, v2, e);
                 if (t > 0.0f) {
                     bool take;
                     if (t < h.t) take = true;
@@ -557,7 +563,7 @@ __device__ inline bool traverse_wave_any(const DeviceBVH &bvh, const TRay &r, fl
                 const uint32_t id = __float_as_uint(v0.w);
                 TriEdges e;
                 if (tri_edges(r, v0, v1, v2, e) && active && id != r.ign0 && id != r.ign1) {
-                    const float t = tri_distance(r, e);
+                    const float t = tri_distance(r, v0, v1, v2, e);
                     if (t > 0.0f && t < tmax) {
                         active = false;
                         tlim = -1.0f;
@@ -677,7 +683,7 @@ __device__ inline Hit traverse_wave_closest(const DeviceBVH &bvh, const TRay &r,
                 const uint32_t id = __float_as_uint(v0.w);
                 TriEdges e;
                 if (tri_edges(r, v0, v1, v2, e) && want && id != r.ign0 && id != r.ign1) {
-                    const float t = tri_distance(r, e);
+                    const float t = tri_distance(r, v0, v1, v2, e);
                     if (t > 0.0f) {
                         bool take;
                         if (t < h.t) take = true;
