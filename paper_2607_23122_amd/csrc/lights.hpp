@@ -226,12 +226,6 @@ __device__ inline bool may_support(const CandTerms &c, float hk, float ak, float
     // (true where nothing can be said: terms beyond the floats)
     return !(fmaxf(fabsf(A), fabsf(B)) > __fmaf_rn(0.5001f, fabsf(c.H + hk), c.slack));
 }
-// term_size of a receiver
-__device__ inline float recv_size(const float o[3], const LightF &L) {
-    const RecvShadow r = recv_shadow(o, L);
-    return term_size(r.hk, r.ak, r.bk, light_scale(L));
-}
-
 // Floats of a receiver's light terms in LDS.
 template <class LT>
 constexpr int kRecvFloats = kBilinear<LT> ? 6 : 3;

@@ -235,6 +235,26 @@ __device__ inline int nth_bit(uint32_t b, int n) {
     return at;
 }
 
+// Strings of NW words shifted by a constant, low word first; zeros enter.
+template <int N, int NW>
+__device__ inline void words_right(const uint32_t (&v)[NW], uint32_t (&out)[NW]) {
+    constexpr int W = N / 32, B = N % 32;
+#pragma unroll
+    for (int i = 0; i < NW; ++i) {
+        const uint32_t lo = i + W < NW ? v[i + W < NW ? i + W : 0] : 0u, hi = i + W + 1 < NW ? v[i + W + 1 < NW ? i + W + 1 : 0] : 0u;
+        out[i] = B ? __builtin_amdgcn_alignbit(hi, lo, B) : lo;
+    }
+}
+template <int N, int NW>
+__device__ inline void words_left(const uint32_t (&v)[NW], uint32_t (&out)[NW]) {
+    constexpr int W = N / 32, B = N % 32;
+#pragma unroll
+    for (int i = 0; i < NW; ++i) {
+        const uint32_t hi = i >= W ? v[i >= W ? i - W : 0] : 0u, lo = i >= W + 1 ? v[i >= W + 1 ? i - W - 1 : 0] : 0u;
+        out[i] = B ? __builtin_amdgcn_alignbit(hi, lo, 32 - B) : hi;
+    }
+}
+
 // Minimum / maximum over the wave as a scalar.  The floats are compared as
 // integers that order alike (negative ones with their lower bits flipped; a NaN
 // lies beyond the infinities), since an integer min or max takes the other

@@ -41,16 +41,21 @@ static inline int r_grid_for(int ntiles) {
     return 8 * ((per + kRTileRun - 1) / kRTileRun) * kRTileRun;
 }
 
-template <int MODE, bool UNB, class LT = LightF>
-__global__ __launch_bounds__(kWinMost, MODE == OCR_AO ? 1 : 6) void reuse_window_kernel(GBufView g, OccView occ, float R2, LT L,
-                                                               const uint32_t *__restrict__ bits, int words, int R,
-                                                               int dark_guard, int accumulate, float *out,
-                                                               int tiles_x, int ntiles, float scale) {
+// RT: the window radius (kOtherRadii: any but the row-task radii).  The pair body
+// is bounded to 6 waves per SIMD (its LDS allows no more at radius 3).
+template <int MODE, bool UNB, class LT, int RT>
+constexpr int kWindowWaves = pair_radius<MODE, UNB, LT>(RT) ? 6 : 1;
+
+template <int MODE, bool UNB, class LT, int RT, int BLOCK>
+__global__ __launch_bounds__(BLOCK, (kWindowWaves<MODE, UNB, LT, RT>)) void reuse_window_kernel(
+    GBufView g, OccView occ, float R2, LT L, const uint32_t *__restrict__ bits, int words, int radius, int dark_guard,
+    int accumulate, float *out, int tiles_x, int ntiles, float scale) {
     extern __shared__ __align__(16) unsigned char smem[];
     int tx, ty;
     r_tile_of_block(tiles_x, ntiles, tx, ty);
     if (ty * tiles_x + tx >= ntiles) return;
-    reuse_window_tile<MODE, UNB, LT>(smem, g, occ, R2, L, bits, words, R, dark_guard, accumulate, out, tx, ty, scale);
+    reuse_window_tile<MODE, UNB, LT, RT, BLOCK>(smem, g, occ, R2, L, bits, words, radius, dark_guard, accumulate, out, tx,
+                                                ty, scale);
 }
 
 // Fixed groups.  Block = 32 x 8 pixels; the group shapes (1x1, 2x1, 2x2,
@@ -224,32 +229,53 @@ __global__ void scale_kernel(float *out, int64_t n, float s) {
 // In frames of at most this many tiles the slowest tile's time is much of the
 // frame's, and eight waves share a tile's candidates instead of four (window 3,
 // 4 / 8 waves: 256x256 AO 17.5 / 11.6 us, boxes 31 / 19; 1280x720 AO 45 / 40,
-// shadows 128 / 102; at 1080p AO 120 / 120, shadows 200 / 211).
-constexpr int kFewTiles = 4096;
+// shadows 128 / 102; at 1080p AO 120 / 120, shadows 200 / 211).  Window 1 has less
+// to share (AO 256x256 .. 640x360 the same, 1280x720 19.1 / 22.5).
+static inline int few_tiles(int R) { return R == 1 ? 1024 : 4096; }
 
-template <int MODE, bool UNB, class LT>
-static hipError_t launch_win(const GBufView &g, const OccView &occ, float R2, const LT &L, const uint32_t *bits,
-                             int words, const ocr_reuse_params &p, float *out, float scale, hipStream_t st) {
+template <int MODE, bool UNB, class LT, int RT, int BLOCK>
+static hipError_t launch_win_t(const GBufView &g, const OccView &occ, float R2, const LT &L, const uint32_t *bits,
+                               int words, const ocr_reuse_params &p, float *out, float scale, hipStream_t st) {
     int tiles_x = (g.w + kWTX - 1) / kWTX, tiles_y = (g.h + kWTY - 1) / kWTY;
     int nt = tiles_x * tiles_y;
-    // (row-task radii; the others' per-wave scratch would take the LDS)
-    const int lanes = kWideTile<MODE, UNB, LT> && nt <= kFewTiles && row_body_radius(p.radius) ? kWinMost : kRBlock;
-    WinLayout lay = win_layout(p.radius, MODE, kPairBody<MODE, UNB, LT>, words, kRecvFloats<LT>, lanes / 64);
+    WinLayout lay = win_layout(p.radius, MODE, pair_radius<MODE, UNB, LT>(p.radius), words, kRecvFloats<LT>, BLOCK / 64);
     // dynamic-LDS limit raised so far (64 KB by default); several host
     // threads may launch at once
     static std::atomic<size_t> attr_bytes{64 * 1024};
     if (lay.total > attr_bytes.load()) {
-        hipError_t e = hipFuncSetAttribute((const void *)reuse_window_kernel<MODE, UNB, LT>,
+        hipError_t e = hipFuncSetAttribute((const void *)reuse_window_kernel<MODE, UNB, LT, RT, BLOCK>,
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lay.total);
         if (e != hipSuccess) return e;
         size_t cur = attr_bytes.load();
         while (cur < lay.total && !attr_bytes.compare_exchange_weak(cur, lay.total)) {
         }
     }
-    dim3 grid(r_grid_for(nt)), block(lanes);
-    hipLaunchKernelGGL((reuse_window_kernel<MODE, UNB, LT>), grid, block, lay.total, st, g, occ, R2, L, bits, words,
-                       p.radius, p.dark_guard, p.accumulate, out, tiles_x, nt, scale);
+    dim3 grid(r_grid_for(nt)), block(BLOCK);
+    hipLaunchKernelGGL((reuse_window_kernel<MODE, UNB, LT, RT, BLOCK>), grid, block, lay.total, st, g, occ, R2, L, bits,
+                       words, p.radius, p.dark_guard, p.accumulate, out, tiles_x, nt, scale);
     return hipSuccess;
+}
+
+template <int MODE, bool UNB, class LT>
+static hipError_t launch_win(const GBufView &g, const OccView &occ, float R2, const LT &L, const uint32_t *bits,
+                             int words, const ocr_reuse_params &p, float *out, float scale, hipStream_t st) {
+    const int64_t nt = (int64_t)((g.w + kWTX - 1) / kWTX) * ((g.h + kWTY - 1) / kWTY);
+    const bool few = nt <= few_tiles(p.radius);
+#define OCR_WIN(RT, BLOCK) launch_win_t<MODE, UNB, LT, RT, BLOCK>(g, occ, R2, L, bits, words, p, out, scale, st)
+    // (the light effects' row tasks keep kRBlock lanes)
+#define OCR_WIN_R(RT)                                                     \
+    if (p.radius == RT) {                                                 \
+        if constexpr (MODE == OCR_AO || pair_radius<MODE, UNB, LT>(RT)) { \
+            if (few) return OCR_WIN(RT, kWinMost);                        \
+        }                                                                 \
+        return OCR_WIN(RT, kRBlock);                                      \
+    }
+    OCR_WIN_R(1)
+    OCR_WIN_R(2)
+    OCR_WIN_R(3)
+    return OCR_WIN(kOtherRadii, kRBlock);
+#undef OCR_WIN_R
+#undef OCR_WIN
 }
 
 template <int MODE, bool UNB, class LT>

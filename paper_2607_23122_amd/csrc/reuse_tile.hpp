@@ -39,19 +39,32 @@ constexpr int kSparse = 8;
 // radius 1 / 2 / 3 unbiased shadows at 1080p 59 / 79 / 135 us with 10 pairs for
 // all, 76 / 92 / 137 with 16, 92 / 126 / 164 with 24.)
 __host__ __device__ constexpr int few_pairs(int R) { return 4 * R; }
-// Which light effects do: several lights' marks cost nearly their densities, so
-// they are left to the row tasks unless validation bits mark the pairs (two
-// lights biased at 1080p 0.50 ms by row tasks, 0.58 by pairs).
+// Which kernels have the pair body and at which radii: the light effects, of one
+// light or with validation bits that mark the pairs (several lights' marks cost
+// nearly their densities: two lights biased at 1080p 0.50 ms by row tasks, 0.58
+// by pairs), and not the biased ones of radius 1, whose 25 densities are cheap
+// (1280x720 boxes 30 us by row tasks, 37 by pairs).
 template <int MODE, bool UNB, class LT>
 constexpr bool kPairBody = MODE != OCR_AO && (UNB || !std::is_same<LT, LightSetF>::value);
-// Whether a window tile's block may have kWinMost lanes.  Several lights' row tasks
-// keep kRBlock, a constant: with a run-time size their kernel, short of scalar
-// registers, reads the lights' constants again in the loops (two lights biased at
-// 1080p 519 us with it, 499 without).
 template <int MODE, bool UNB, class LT>
-constexpr bool kWideTile = MODE == OCR_AO || kPairBody<MODE, UNB, LT>;
-// Counters ahead of the candidate list: candidates, cursor, largest term_size
-// (as its bits), candidates left to the row tasks, their cursor.
+__host__ __device__ constexpr bool pair_radius(int R) {
+    return kPairBody<MODE, UNB, LT> && R <= 3 && R >= (UNB ? 1 : 2);
+}
+// Biased: a tile with at most this many candidates leaves them to the row tasks,
+// which need no marks first: a batch of marks costs about as much as the rows of
+// 13 candidates at radius 3 (five candidates in a 48x36 frame 9 us, 17 by pairs).
+// In the small frames that kWinMost lanes are for, as many as one round of the
+// waves takes.
+__host__ __device__ constexpr int few_candidates(int R, int block) {
+    return block > kRBlock ? block / 64 * (64 / (4 * R + 1)) : 16;
+}
+// The radii a window kernel is compiled for: one of the row-task radii, all others
+// (at run time), or any (the batched schedule).  Apart, each has the registers it
+// needs: with all in one kernel, the pair body's cost the others 3 to 9%.
+constexpr int kAnyRadius = -1, kOtherRadii = 0;
+// Counters ahead of the candidate list: candidates, their cursor, largest
+// term_size (as its bits), whether the row tasks have candidates of the pair
+// body's, and their cursor.
 constexpr int kListHead = 8;
 
 __device__ inline void ld3(const float *p, int64_t i, float v[3]) {
@@ -115,7 +128,7 @@ __host__ __device__ constexpr bool row_body_radius(int R) { return R >= 1 && R <
 // LDS layout of the window kernel for radius R (dynamic shared memory).
 struct WinLayout {
     int RWX, RWY, cells, side, dens, hsum, words;
-    size_t o_off, n_off, sh_off, valid_off, miss_off, list_off, many_off, B_off, wave_off, total;
+    size_t o_off, n_off, sh_off, flag_off, row_off, list_off, left_off, B_off, wave_off, total;
 };
 
 __host__ __device__ constexpr size_t lds_take(size_t &off, size_t bytes) {
@@ -125,7 +138,7 @@ __host__ __device__ constexpr size_t lds_take(size_t &off, size_t bytes) {
 }
 
 // nrecv: floats of a receiver's light terms (kRecvFloats of the light type);
-// waves: of the block; pairs: kPairBody of the kernel.
+// waves: of the block; pairs: pair_radius of the kernel.
 __host__ __device__ constexpr WinLayout win_layout(int R, int mode, bool pairs, int words, int nrecv = 3,
                                                    int waves = kRBlock / 64) {
     WinLayout l{};
@@ -141,15 +154,15 @@ __host__ __device__ constexpr WinLayout win_layout(int R, int mode, bool pairs, 
     l.o_off = lds_take(off, sizeof(float) * 3 * l.cells);
     l.n_off = lds_take(off, sizeof(float) * 3 * l.cells);
     l.sh_off = lds_take(off, mode != OCR_AO ? sizeof(float) * nrecv * l.cells : 0);
-    l.valid_off = lds_take(off, l.cells);
-    l.miss_off = lds_take(off, l.cells);
+    l.flag_off = lds_take(off, l.cells);
+    l.row_off = lds_take(off, mode != OCR_AO ? sizeof(uint32_t) * l.RWY : 0);
     l.list_off = lds_take(off, kListHead * sizeof(int) + sizeof(uint16_t) * l.cells);
-    // the candidates that the pair lanes leave to the row tasks
-    l.many_off = lds_take(off, row_body_radius(R) && pairs ? sizeof(uint16_t) * l.cells : 0);
+    // the candidates that the pair lanes leave to the row tasks, a bit each
+    l.left_off = lds_take(off, pairs ? (l.cells + 63) / 64 * sizeof(unsigned long long) : 0);
     // per-wave scratch: the per-candidate body's densities and box sums (the
     // row-task body keeps its sums in registers), the pair lanes' candidates
-    const int per_wave = !row_body_radius(R) ? l.dens + l.hsum : (pairs ? 64 : 0);
-    l.wave_off = lds_take(off, sizeof(float) * waves * per_wave);
+    const int per_wave = !row_body_radius(R) ? (int)sizeof(float) * (l.dens + l.hsum) : (pairs ? 64 : 0);
+    l.wave_off = lds_take(off, (size_t)waves * per_wave);
     l.total = off;
     return l;
 }
@@ -224,17 +237,19 @@ __device__ inline float from_prev_lane(float v) {
 // lane r + R and scatters p_i(j) / P_i(j) as the per-candidate body does.
 // The sums run in the same order as that body's, so the estimates are the
 // same bits.
-template <int MODE, bool UNB, class LT, int R>
+//
+// MARKED: of the candidates listed, those whose bits are set in s_left (what the
+// pair body left); a batch then spans the others.
+template <int MODE, bool UNB, class LT, int R, bool MARKED>
 __device__ inline void tile_row_candidates(const WinLayout &lay, unsigned char *smem, const GBufView &g,
                                            const OccView &occ, float R2, const LT &L,
-                                           const uint32_t *__restrict__ bits, int words, int tx, int ty,
-                                           const uint16_t *s_list, const int *s_end, int *s_cursor) {
+                                           const uint32_t *__restrict__ bits, int words, int tx, int ty) {
     constexpr int TW = 2 * R + 1, SIDE = 4 * R + 1, D = 2 * R;
     constexpr int TX = kWTX, TY = kWTY, RW = kWTX + 2 * R, CELLS = RW * (kWTY + 2 * R);
     // The staged normals and light terms follow the positions directly
     // (3 * CELLS floats each, a multiple of 16 bytes), so all the receiver
     // values a density reads sit at constant offsets from one LDS address.
-    constexpr WinLayout kLay = win_layout(R, MODE, kPairBody<MODE, UNB, LT>, 1, kRecvFloats<LT>);
+    constexpr WinLayout kLay = win_layout(R, MODE, MARKED, 1, kRecvFloats<LT>);
     static_assert(kLay.cells == CELLS && kLay.n_off == kLay.o_off + 3 * CELLS * sizeof(float) &&
                       (MODE == OCR_AO || kLay.sh_off == kLay.n_off + 3 * CELLS * sizeof(float)),
                   "receiver arrays are contiguous");
@@ -245,8 +260,13 @@ __device__ inline void tile_row_candidates(const WinLayout &lay, unsigned char *
     const float *s_sh = s_n + 3 * CELLS;
     const int lane = threadIdx.x & 63;
     const int x0 = tx * TX - R, y0 = ty * TY - R;
-    // candidates s_list[0, *s_end), and the shared cursor (entries claimed)
-    const int end = *s_end;
+    // s_count[0] candidates listed; the shared cursor counts the entries claimed,
+    // zero at the tile's start
+    int *s_count = reinterpret_cast<int *>(smem + lay.list_off);
+    const uint16_t *s_list = reinterpret_cast<const uint16_t *>(smem + lay.list_off + kListHead * sizeof(int));
+    const unsigned long long *s_left = reinterpret_cast<const unsigned long long *>(smem + lay.left_off);
+    int *s_cursor = &s_count[MARKED ? 4 : 1];
+    const int end = s_count[0];
     for (;;) {
         const int cur = __builtin_amdgcn_readfirstlane(__atomic_load_n(s_cursor, __ATOMIC_RELAXED));
         if (cur >= end) break;
@@ -258,6 +278,7 @@ __device__ inline void tile_row_candidates(const WinLayout &lay, unsigned char *
             c = s_list[ci];
             const int cy = small_div(c, inv_rw), cx = c - __mul24(cy, RW);
             hd = cand_rect(cx, cy, R).nty + 2 * R;
+            if (MARKED && !((s_left[ci >> 6] >> (ci & 63)) & 1ull)) hd = 0;
         }
         const int rows_inc = wave_incl_scan(hd);
         const int nb = __popcll(wave_ballot(ci < end && rows_inc <= 64));
@@ -271,8 +292,17 @@ __device__ inline void tile_row_candidates(const WinLayout &lay, unsigned char *
 
         // this lane's candidate and receiver row
         int k = 0;
-        for (int m = 0; m < nb; ++m) k += lane >= __builtin_amdgcn_readlane(rows_inc, m) ? 1 : 0;
-        k = min(k, nb - 1);
+        if constexpr (MARKED) {
+            if (rows_total == 0) continue;
+            const unsigned long long have = wave_ballot(hd > 0 && rows_inc <= 64);
+            for (unsigned long long m = have; m != 0ull; m &= m - 1ull) {
+                const int i = (int)__builtin_ctzll(m);
+                k = lane >= __builtin_amdgcn_readlane(rows_exc, i) ? i : k;
+            }
+        } else {
+            for (int m = 0; m < nb; ++m) k += lane >= __builtin_amdgcn_readlane(rows_inc, m) ? 1 : 0;
+            k = min(k, nb - 1);
+        }
         const int cl = __shfl(c, k), rs = __shfl(rows_exc, k);
         const int cy = small_div(cl, inv_rw), cx = cl - __mul24(cy, RW);
         const CandRect q = cand_rect(cx, cy, R);
@@ -302,10 +332,7 @@ __device__ inline void tile_row_candidates(const WinLayout &lay, unsigned char *
             const int kcb = __mul24(ky, RW) + kx0;
 #pragma unroll
             for (int e = 0; e < SIDE; ++e) {
-                // (candidates left by the pair body have many positive
-                // densities: all are evaluated, without a branch for each)
-                const bool on = e < WD && ((rowbits >> e) & 1u);
-                if (kPairBody<MODE, UNB, LT> || on) {
+                if (e < WD && ((rowbits >> e) & 1u)) {
                     const int kc = kcb + e;
                     const float ok[3] = {s_o[kc], s_o[CELLS + kc], s_o[2 * CELLS + kc]};
                     const float nk[3] = {s_n[kc], s_n[CELLS + kc], s_n[2 * CELLS + kc]};
@@ -316,8 +343,7 @@ __device__ inline void tile_row_candidates(const WinLayout &lay, unsigned char *
                     } else {
                         float v[kRecvFloats<LT>];
                         for (int a = 0; a < kRecvFloats<LT>; ++a) v[a] = s_sh[a * CELLS + kc];
-                        const float d = dens_light(w, nk, recv_load(v, L), nzj, L);
-                        p[e] = !kPairBody<MODE, UNB, LT> || on ? d : 0.0f;
+                        p[e] = dens_light(w, nk, recv_load(v, L), nzj, L);
                     }
                 }
             }
@@ -369,7 +395,7 @@ __device__ inline void tile_row_candidates(const WinLayout &lay, unsigned char *
 // column order: it evaluates the density and sums P_i(j) over the candidate's
 // pairs in the target's window, row by row, by cross-lane reads: the box sums
 // without their zeros, so the same bits.  Candidates with more than few_pairs(R)
-// marks are listed in s_many for the row tasks.
+// marks are left to the row tasks (s_left, all ones at the tile's start).
 // 1080p, window 3, one light: biased 0.275 -> 0.200 ms (1.41e8 -> 0.67e8 VALU
 // instructions), unbiased 0.207 -> 0.137 (0.24e8).  What is left is the tail:
 // without the few tiles that hold hundreds of candidates for the row tasks
@@ -388,11 +414,11 @@ __device__ inline void tile_pair_candidates(const WinLayout &lay, unsigned char 
     const float *s_sh = reinterpret_cast<const float *>(smem + lay.sh_off);
     int *s_count = reinterpret_cast<int *>(smem + lay.list_off);
     const uint16_t *s_list = reinterpret_cast<const uint16_t *>(smem + lay.list_off + kListHead * sizeof(int));
-    uint16_t *s_many = reinterpret_cast<uint16_t *>(smem + lay.many_off);
-    int *l_own = reinterpret_cast<int *>(smem + lay.wave_off) + (threadIdx.x >> 6) * 64;
+    unsigned long long *s_left = reinterpret_cast<unsigned long long *>(smem + lay.left_off);
+    uint8_t *l_own = smem + lay.wave_off + (threadIdx.x >> 6) * 64;
     const int lane = threadIdx.x & 63;
     const int x0 = tx * TX - R, y0 = ty * TY - R;
-    const int ncand = s_count[0];
+    const int ncand = __builtin_amdgcn_readfirstlane(s_count[0]);
     const float qmax = __int_as_float(s_count[2]);
     for (;;) {
         int base = 0;
@@ -410,25 +436,28 @@ __device__ inline void tile_pair_candidates(const WinLayout &lay, unsigned char 
 #pragma unroll
             for (int i = 0; i < NW; ++i) w[i] = bits[gj * words + i];
         } else {
+            uint32_t v[NW];
 #pragma unroll
-            for (int i = 0; i < NW; ++i) w[i] = 0u;
+            for (int i = 0; i < NW; ++i) v[i] = 0u;
             float dzj[3];
             ld3(occ.dz, gj, dzj);
             const CandTerms t = cell_terms(s_sh, CELLS, c, dzj, L, qmax);
             const int here = min(ncand - base, 64), most = here - here / 8;
             int marks = 0;
 #pragma unroll 1
-            for (int y = 0; y < SIDE; ++y) {
-                // (a row outside the staged cells is read from the nearest one
-                // and masked below; a column beyond them reads a neighbour row)
+            for (int i0 = 0; i0 < SIDE; ++i0) {
+                // the candidate's own row, where a large light's marks are, and
+                // those below it first.  (A row outside the staged cells is read
+                // from the nearest one and masked below; a column beyond them
+                // reads a neighbour row.)
+                const int y = i0 <= D ? D + i0 : i0 - D - 1;
                 const int k0 = __mul24(min(max(cy - D + y, 0), RH - 1), RW) + (cx - D);
                 uint32_t m = 0;
 #pragma unroll
                 for (int e = 0; e < SIDE; ++e) m |= cell_support(s_sh, CELLS, k0 + e, t) ? 1u << e : 0u;
                 // under a large light most candidates have many pairs: once seven
-                // in eight have, the batch goes to the row tasks (a 24 m light 8 m
-                // above the terrain: 360 -> 342 us, 302 by row tasks alone; at
-                // three in four 331, but the boxes' 333x197 frame 36 -> 41)
+                // in eight of a batch have, it and those not claimed yet are left
+                // to the row tasks
                 marks += __popc(m);
                 if (__popcll(wave_ballot(has && marks > few_pairs(R))) > most) {
                     dense = true;
@@ -436,14 +465,28 @@ __device__ inline void tile_pair_candidates(const WinLayout &lay, unsigned char 
                 }
                 // the row's bits enter above the earlier ones
 #pragma unroll
-                for (int i = 0; i < NW - 1; ++i) w[i] = __builtin_amdgcn_alignbit(w[i + 1], w[i], SIDE);
-                w[NW - 1] = (w[NW - 1] >> SIDE) | (m << (32 - SIDE));
+                for (int i = 0; i < NW - 1; ++i) v[i] = __builtin_amdgcn_alignbit(v[i + 1], v[i], SIDE);
+                v[NW - 1] = (v[NW - 1] >> SIDE) | (m << (32 - SIDE));
             }
-            // down to bit 0
-            constexpr int kRest = 32 * NW - SIDE * SIDE;
+            if (!dense) {
+                // down to bit 0, and the rows in order: the last D come first
+                constexpr int kRest = 32 * NW - SIDE * SIDE;
+                uint32_t hi[NW], lo[NW];
+                words_right<kRest + (D + 1) * SIDE>(v, hi);
+                words_right<kRest>(v, lo);
+                words_left<D * SIDE>(lo, w);
 #pragma unroll
-            for (int i = 0; i < NW - 1; ++i) w[i] = __builtin_amdgcn_alignbit(w[i + 1], w[i], kRest);
-            w[NW - 1] >>= kRest;
+                for (int i = 0; i < NW; ++i) w[i] |= hi[i];
+            }
+        }
+        if (dense) {
+            // (Its bits of s_left stay set, and no entry is left to claim.  By
+            // every lane: after a branch on lane 0 the compiler may send the
+            // others past the claim's, and they would not wait for lane 0's.)
+            s_count[3] = 1;
+            s_count[1] = ncand;
+            wave_sync();
+            continue;
         }
         // the receivers that the candidate's targets of this tile need
         const CandRect q = cand_rect(cx, cy, R);
@@ -465,17 +508,13 @@ __device__ inline void tile_pair_candidates(const WinLayout &lay, unsigned char 
             w[i] = has ? w[i] & keep[i] : 0u;
             cnt += __popc(w[i]);
         }
-        const bool many = has && (dense || cnt > few_pairs(R));
+        const bool many = has && cnt > few_pairs(R);
         const unsigned long long mm = wave_ballot(many);
-        if (mm != 0ull) {
-            int at = 0;
-            if (lane == 0) at = atomicAdd(&s_count[3], (int)__popcll(mm));
-            at = __builtin_amdgcn_readfirstlane(at);
-            if (many) {
-                s_many[at + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mm >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mm, 0u))] = (uint16_t)c;
-                cnt = 0;
-            }
+        if (lane == 0) {
+            s_left[base >> 6] = mm;
+            if (mm != 0ull) s_count[3] = 1;
         }
+        if (many) cnt = 0;
         const int incl = wave_incl_scan(cnt), excl = incl - cnt, total = __builtin_amdgcn_readlane(incl, 63);
         // lanes for the pairs of as many candidates at a time as 64 hold
         for (int done = 0; done < total;) {
@@ -486,9 +525,9 @@ __device__ inline void tile_pair_candidates(const WinLayout &lay, unsigned char 
             // number at its first pair, then the largest so far), and its place
             // among that one's pairs
             l_own[lane] = 0;
-            if (take) l_own[excl - done] = lane;
+            if (take) l_own[excl - done] = (uint8_t)lane;
             wave_sync();
-            const int own = wave_incl_max(l_own[lane]);
+            const int own = wave_incl_max((int)l_own[lane]);
             wave_sync();
             const bool pair = lane < upto - done;
             const int first = __shfl(excl, own) - done, n = __shfl(cnt, own);
@@ -570,43 +609,58 @@ __device__ inline void tile_pair_candidates(const WinLayout &lay, unsigned char 
     }
 }
 
-// All candidates of a staged tile, row-task radii.
-template <int MODE, bool UNB, class LT, int R>
+// All candidates of a staged tile, row-task radii; BLOCK lanes call it.
+template <int MODE, bool UNB, class LT, int R, int BLOCK>
 __device__ inline void tile_candidates(const WinLayout &lay, unsigned char *smem, const GBufView &g,
                                        const OccView &occ, float R2, const LT &L,
                                        const uint32_t *__restrict__ bits, int words, int tx, int ty) {
-    int *s_count = reinterpret_cast<int *>(smem + lay.list_off);
-    const uint16_t *s_list = reinterpret_cast<const uint16_t *>(smem + lay.list_off + kListHead * sizeof(int));
-    if constexpr (kPairBody<MODE, UNB, LT>) {
-        tile_pair_candidates<MODE, UNB, LT, R>(lay, smem, g, occ, L, bits, words, tx, ty);
-        __syncthreads();
-        if (s_count[3] > 0)
-            tile_row_candidates<MODE, UNB, LT, R>(lay, smem, g, occ, R2, L, bits, words, tx, ty,
-                                                  reinterpret_cast<const uint16_t *>(smem + lay.many_off), &s_count[3],
-                                                  &s_count[4]);
+    if constexpr (pair_radius<MODE, UNB, LT>(R)) {
+        int *s_count = reinterpret_cast<int *>(smem + lay.list_off);
+        bool rows = !UNB && __builtin_amdgcn_readfirstlane(s_count[0]) <= few_candidates(R, BLOCK);
+        if (!rows) {
+            if constexpr (!UNB) {
+                // the largest term_size of the receivers (1 for cells without one;
+                // floats from 0 up order as integers)
+                constexpr int CELLS = (kWTX + 2 * R) * (kWTY + 2 * R);
+                const float *s_sh = reinterpret_cast<const float *>(smem + lay.sh_off);
+                const LightScale sc = light_scale(L);
+                float q = 0.0f;
+                for (int c = threadIdx.x; c < CELLS; c += BLOCK)
+                    q = fmaxf(q, term_size(s_sh[c], s_sh[CELLS + c], s_sh[2 * CELLS + c], sc));
+                const int m = ~wave_min_i(~__float_as_int(q));
+                if ((threadIdx.x & 63) == 0) atomicMax(&s_count[2], m);
+                __syncthreads();
+            }
+            tile_pair_candidates<MODE, UNB, LT, R>(lay, smem, g, occ, L, bits, words, tx, ty);
+            __syncthreads();
+            rows = __builtin_amdgcn_readfirstlane(s_count[3]) != 0;
+        }
+        if (rows) tile_row_candidates<MODE, UNB, LT, R, true>(lay, smem, g, occ, R2, L, bits, words, tx, ty);
     } else {
-        tile_row_candidates<MODE, UNB, LT, R>(lay, smem, g, occ, R2, L, bits, words, tx, ty, s_list, &s_count[0],
-                                              &s_count[1]);
+        tile_row_candidates<MODE, UNB, LT, R, false>(lay, smem, g, occ, R2, L, bits, words, tx, ty);
     }
 }
 
 // One kWTX x kWTY target tile (tx, ty) of the sliding-window estimator; every
-// thread of the block calls it.  `smem` holds win_layout(R, ...).total bytes.
-template <int MODE, bool UNB, class LT = LightF>
+// thread of the block calls it.  `smem` holds win_layout(radius, ...).total bytes.
+// RT: the radius it is compiled for.
+template <int MODE, bool UNB, class LT = LightF, int RT = kAnyRadius, int BLOCK = kRBlock>
 __device__ inline void reuse_window_tile(unsigned char *smem, const GBufView &g, const OccView &occ, float R2,
-                                         const LT &L, const uint32_t *__restrict__ bits, int words, int R,
+                                         const LT &L, const uint32_t *__restrict__ bits, int words, int radius,
                                          int dark_guard, int accumulate, float *out, int tx, int ty,
                                          float scale = 1.0f) {
-    const int block = kWideTile<MODE, UNB, LT> ? (int)blockDim.x : kRBlock;
-    const WinLayout lay = win_layout(R, MODE, kPairBody<MODE, UNB, LT>, words, kRecvFloats<LT>, block >> 6);
+    const int R = RT > 0 ? RT : radius;
+    const bool pairs = pair_radius<MODE, UNB, LT>(R);
+    const WinLayout lay = win_layout(R, MODE, pairs, words, kRecvFloats<LT>, BLOCK / 64);
     const int TX = kWTX, TY = kWTY, RW = lay.RWX, CELLS = lay.cells, D = 2 * R, SIDE = lay.side, TW = 2 * R + 1;
     const float inv_rw = 1.0f / (float)RW;
     unsigned long long *s_B = reinterpret_cast<unsigned long long *>(smem + lay.B_off);
     float *s_o = reinterpret_cast<float *>(smem + lay.o_off);    // [3][cells]
     float *s_n = reinterpret_cast<float *>(smem + lay.n_off);    // [3][cells]
     float *s_sh = reinterpret_cast<float *>(smem + lay.sh_off);  // [kRecvFloats][cells]
-    uint8_t *s_valid = smem + lay.valid_off;
-    uint8_t *s_miss = smem + lay.miss_off;
+    uint8_t *s_flag = smem + lay.flag_off;  // bit 0: a receiver, bit 1: whose ray hit nothing
+    // the latter as a mask per row, for the dark-region guard (at most 32 columns)
+    uint32_t *s_row = reinterpret_cast<uint32_t *>(smem + lay.row_off);
     int *s_count = reinterpret_cast<int *>(smem + lay.list_off);
     uint16_t *s_list = reinterpret_cast<uint16_t *>(smem + lay.list_off + kListHead * sizeof(int));
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -616,13 +670,13 @@ __device__ inline void reuse_window_tile(unsigned char *smem, const GBufView &g,
     const int x0 = tx * TX - R, y0 = ty * TY - R;
     const int tid = threadIdx.x;
     if (tid < kListHead) s_count[tid] = 0;
-    for (int t = tid; t < TX * TY; t += block) s_B[t] = 0ull;
+    if (pairs && tid < 8) reinterpret_cast<unsigned long long *>(smem + lay.left_off)[min(tid, (CELLS - 1) / 64)] = ~0ull;
+    for (int t = tid; t < TX * TY; t += BLOCK) s_B[t] = 0ull;
     __syncthreads();
 
     // Stage receivers (o, n, shadow terms), validity, misses, validation
     // bits, and compact the cells whose ray found an occluder.
-    float qmax = 0.0f;
-    for (int c = tid; c < CELLS; c += block) {
+    for (int c = tid; c < CELLS; c += BLOCK) {
         const int cyy = small_div(c, inv_rw);
         int gx = x0 + (c - __mul24(cyy, RW)), gy = y0 + cyy;
         bool inside = gx >= 0 && gx < g.w && gy >= 0 && gy < g.h;
@@ -646,29 +700,30 @@ __device__ inline void reuse_window_tile(unsigned char *smem, const GBufView &g,
             float v[kRecvFloats<LT>] = {};
             if (valid) recv_store(recv_of(o, L), v);
             for (int a = 0; a < kRecvFloats<LT>; ++a) s_sh[a * CELLS + c] = v[a];
-            if constexpr (kPairBody<MODE, UNB, LT> && !UNB) {
-                if (valid && row_body_radius(R)) qmax = fmaxf(qmax, recv_size(o, L));
-            }
         }
-        s_valid[c] = valid;
-        s_miss[c] = valid && hit == OCR_HIT_MISS;
+        s_flag[c] = (uint8_t)((valid ? 1 : 0) | (valid && hit == OCR_HIT_MISS ? 2 : 0));
         if (valid && hit < OCR_HIT_SELF) s_list[atomicAdd(s_count, 1)] = (uint16_t)c;
-    }
-    if (kPairBody<MODE, UNB, LT> && !UNB && row_body_radius(R)) {
-        // (floats from 0 up order as integers)
-        const int m = ~wave_min_i(~__float_as_int(qmax));
-        if (lane == 0) atomicMax(&s_count[2], m);
     }
     __syncthreads();
 
-    if (R == 1) {
-        tile_candidates<MODE, UNB, LT, 1>(lay, smem, g, occ, R2, L, bits, words, tx, ty);
-    } else if (R == 2) {
-        tile_candidates<MODE, UNB, LT, 2>(lay, smem, g, occ, R2, L, bits, words, tx, ty);
-    } else if (R == 3) {
-        tile_candidates<MODE, UNB, LT, 3>(lay, smem, g, occ, R2, L, bits, words, tx, ty);
-    } else {
-        // Other radii: one wave per candidate j (kRBlock lanes, see the launch).
+    // (read after the candidates' barrier; the window byte by byte, 49 reads a
+    // target at radius 3, was a fifth of the biased shadows' time)
+    if (MODE != OCR_AO && dark_guard && tid < lay.RWY) {
+        uint32_t m = 0;
+        for (int x = 0; x < RW; ++x) m |= (uint32_t)(s_flag[tid * RW + x] >> 1) << x;
+        s_row[tid] = m;
+    }
+
+#define OCR_TILE_RADIUS(r)                                                                                   \
+    if constexpr (RT == kAnyRadius || RT == r) {                                                             \
+        if (R == r) tile_candidates<MODE, UNB, LT, r, BLOCK>(lay, smem, g, occ, R2, L, bits, words, tx, ty); \
+    }
+    OCR_TILE_RADIUS(1)
+    OCR_TILE_RADIUS(2)
+    OCR_TILE_RADIUS(3)
+#undef OCR_TILE_RADIUS
+    if ((RT == kAnyRadius || RT == kOtherRadii) && !row_body_radius(R)) {
+        // Other radii: one wave per candidate j.
         const int ncand = *s_count;
         for (int li = wave; li < ncand; li += kRBlock >> 6) {
             const int c = __builtin_amdgcn_readfirstlane((int)s_list[li]);
@@ -825,12 +880,12 @@ __device__ inline void reuse_window_tile(unsigned char *smem, const GBufView &g,
     __syncthreads();
 
     // one lane per target
-    for (int t = tid; t < TX * TY; t += block) {
+    for (int t = tid; t < TX * TY; t += BLOCK) {
         const int ix = t % TX, iy = t / TX;
         const int px = tx * TX + ix, py = ty * TY + iy;
         if (px >= g.w || py >= g.h) continue;
         const int c = __mul24(iy + R, RW) + (ix + R);
-        const bool valid = s_valid[c];
+        const bool valid = s_flag[c] & 1;
         float B = (float)((double)s_B[t] * 0x1p-32);
         float F = 1.0f;
         bool dark = false;
@@ -849,10 +904,9 @@ __device__ inline void reuse_window_tile(unsigned char *smem, const GBufView &g,
                 F = front_light(o, n, L);
             }
             if (dark_guard) {
-                int misses = 0;
-                for (int dy = -R; dy <= R; ++dy)
-                    for (int dx = -R; dx <= R; ++dx) misses += s_miss[c + dy * RW + dx];
-                dark = misses == 0;
+                uint32_t seen = 0;
+                for (int dy = 0; dy < TW; ++dy) seen |= s_row[iy + dy];
+                dark = ((seen >> ix) & ((1u << TW) - 1u)) == 0u;
             }
         }
         const int64_t gi = (int64_t)py * g.w + px;

@@ -77,3 +77,76 @@ def test_marked_bits_equal_counted(light, size):
         assert cand.any()
         for b in bits[:-1]:
             assert np.array_equal(b[cand], bits[-1][cand])
+
+
+# Which body sums a candidate is chosen by its marks alone, so a frame can be sent
+# through the row tasks: marks that carry a density of zero (the pairs that even
+# without occluders have none) change no sum, and candidates with that many marks
+# are left to them.
+_EFFECTS = ["shadow", "bilinear", "solid_angle", "solid_angle_bilinear", "direct", "lights"]
+
+
+def _reuse(ocr, effect, dg, occ, lt, p, ws=None, bvh=None):
+    import torch
+    out = torch.empty((dg.height, dg.width), device="cuda")
+    if effect in ("shadow", "bilinear", "lights"):
+        ocr.reuse_shadow(bvh, dg, occ, lt, p, out, ws)
+    elif effect.startswith("solid_angle"):
+        ocr.reuse_shadow_solid_angle(bvh, dg, occ, lt, p, out, ws)
+    else:
+        ocr.reuse_direct_illumination(bvh, dg, occ, lt, p, 100.0, 0.8, out, ws)
+    return out.cpu().numpy().view(np.uint32)
+
+
+@pytest.mark.parametrize("effect", _EFFECTS)
+@pytest.mark.parametrize("light,size", [("near", (61, 37)), ("near", (333, 197)), ("oblong", (333, 197)),
+                                        ("large", (333, 197)), ("far", (1367, 771))])
+def test_pair_body_equals_row_tasks_to_the_bit(light, size, effect):
+    import copy
+    import torch
+    import paper_2607_23122_amd as ocr
+    scene, gb, lt = _frame(light, size)
+    if effect.endswith("bilinear"):
+        lt = copy.copy(lt)
+        lt.pdf = 1
+    uniform = copy.copy(lt)
+    uniform.pdf = 0
+    if effect == "lights":
+        second = w.RectLight(lt.center + np.float32([3, 0.5, 1]), lt.edge_u, lt.edge_v)
+        lt = uniform = [lt, second]
+    bvh = ocr.build_bvh(scene.V, scene.F)
+    # no occluder near any segment
+    away = ocr.build_bvh(np.array([[0, -900, 0], [1, -900, 0], [0, -900, 1]], np.float32), np.array([[0, 1, 2]], np.uint32))
+    dg = ocr.DeviceGBuffer.from_host(gb)
+    occ = ocr.trace_occluders(bvh, dg, "shadow", 1.0, lt, 5, 0)
+    n = size[0] * size[1]
+    cand = (occ.hit_u32() < 0xFFFFFFFE).ravel()
+    for radius in (1, 2, 3):
+        log(f"[pairs] rows {light} {size} {effect} window {radius}")
+        p = ocr.reuse_params("window", radius, 8, "unbiased", validated=True)
+        words = ((4 * radius + 1) ** 2 + 31) // 32
+
+        def bits_of(hierarchy):
+            ws = torch.zeros(ocr.workspace_bytes(gb.width, gb.height, p), dtype=torch.uint8, device="cuda")
+            ocr.validate_pairs(hierarchy, dg, occ, "shadow", 1.0, uniform, p, ws)
+            return ws
+
+        true, every = bits_of(bvh), bits_of(away)
+        full = (1 << (4 * radius + 1) ** 2) - 1
+        mask = np.array([(full >> (32 * i)) & 0xFFFFFFFF for i in range(words)], np.uint32)
+        # biased: every mark set, so each candidate takes the row tasks
+        biased = ocr.reuse_params("window", radius, 8, "biased", dark_guard=False)
+        marked = true.clone()
+        marked.view(torch.int32)[:n * words] = torch.from_numpy(np.tile(mask, n).view(np.int32)).cuda()
+        assert np.array_equal(_reuse(ocr, effect, dg, occ, lt, biased),
+                              _reuse(ocr, effect, dg, occ, lt, p, marked, bvh))
+        # unbiased: the pairs without a density marked besides
+        b = true.cpu().numpy()[:4 * n * words].view(np.uint32).reshape(n, words)
+        e = every.cpu().numpy()[:4 * n * words].view(np.uint32).reshape(n, words)
+        both = b | (mask & ~e)
+        few = np.unpackbits(b[cand].view(np.uint8), axis=1).sum(1) <= 4 * radius
+        log(f"    candidates {int(cand.sum())}, with few pairs {int(few.sum())}, of these moved "
+            f"{int((np.unpackbits(both[cand][few].view(np.uint8), axis=1).sum(1) > 4 * radius).sum())}")
+        moved = true.clone()
+        moved.view(torch.int32)[:n * words] = torch.from_numpy(both.view(np.int32).ravel().copy()).cuda()
+        assert np.array_equal(_reuse(ocr, effect, dg, occ, lt, p, true, bvh), _reuse(ocr, effect, dg, occ, lt, p, moved, bvh))
