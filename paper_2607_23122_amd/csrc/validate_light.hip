@@ -36,6 +36,14 @@ constexpr int kFewMarks = 8;
 // 119000 candidates, runs of 1 / 2 / 4: 0.230 / 0.185 / 0.176 ms; 1280x720 terrain
 // with few such candidates 0.195 / 0.209 / 0.253).
 constexpr uint32_t kManyStep = 16384;
+// Candidates of few marks per further one in a run (1 to 6).  Neighbours in the
+// list may lie far apart in the frame, and a wave walks the union of their paths:
+// in a large mesh, where those are long, a wave for each is the shorter way as
+// long as there are waves (1.16M triangles 333x197, 73 candidates: 69 us by sixes,
+// 37 alone; 291000 triangles 1280x720, 10000 candidates: 104 / 83); in a small one
+// they share most of theirs (1154 triangles 333x197: 24 us by sixes, 33 alone).
+constexpr uint32_t kFewStep = 8192, kFewStepSmall = 256;
+constexpr int64_t kSmallMesh = 16384;
 
 // Appends the wave's lanes that have something to a counted list (every lane
 // calls it).
@@ -127,8 +135,13 @@ __global__ __launch_bounds__(kLBlock) void mark_pairs_kernel(GBufView g, OccView
     }
     __syncthreads();
 
-    const int base = wave * 64;
-    if (base >= ncand) return;  // (no barrier follows)
+    // a wave per 64 candidates; of few, the rows of the square are shared by all
+    // four waves (48x36 boxes, two lights, window 3 42 -> 35 us; 1080p
+    // terrain under a light 950 m away 52 -> 47)
+    const int parts = ncand <= 64 ? 4 : ncand <= 128 ? 2 : 1, part = wave & (parts - 1);
+    const int base = (wave / parts) * 64;
+    if (base >= ncand) return;  // (parts is 1: no barrier follows)
+    const int row0 = part * SIDE / parts, row1 = (part + 1) * SIDE / parts;
     const bool has = base + lane < ncand;
     const int id = s_list[has ? base + lane : base];
     // the candidate's pixel in the tile and on the image
@@ -158,8 +171,10 @@ __global__ __launch_bounds__(kLBlock) void mark_pairs_kernel(GBufView g, OccView
         for (int y = 0; y < SIDE; ++y) {
             const int k0 = __mul24(ly + y, RW) + lx;
             uint32_t m = 0;
+            if (y >= row0 && y < row1) {
 #pragma unroll
-            for (int e = 0; e < SIDE; ++e) m |= cell_support(p, CELLS, k0 + e, ct) ? 1u << e : 0u;
+                for (int e = 0; e < SIDE; ++e) m |= cell_support(p, CELLS, k0 + e, ct) ? 1u << e : 0u;
+            }
             // the row's bits enter above the earlier ones
 #pragma unroll
             for (int i = 0; i < NW - 1; ++i) v[i] = __builtin_amdgcn_alignbit(v[i + 1], v[i], SIDE);
@@ -169,6 +184,20 @@ __global__ __launch_bounds__(kLBlock) void mark_pairs_kernel(GBufView g, OccView
         constexpr int kRest = 32 * NW - SIDE * SIDE;
 #pragma unroll
         for (int i = 0; i < NW; ++i) w[i] |= i < NW - 1 ? __builtin_amdgcn_alignbit(v[i < NW - 1 ? i + 1 : i], v[i], kRest) : v[i] >> kRest;
+    }
+    if (parts > 1) {
+        // the other waves' rows, through the light terms' LDS
+        static_assert(256 * NW <= 3 * CELLS, "room for the words");
+        uint32_t *s_w = reinterpret_cast<uint32_t *>(s_t);
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < NW; ++i) s_w[i * kLBlock + tid] = w[i];
+        __syncthreads();
+        if (part > 0) return;
+        for (int o = 1; o < parts; ++o) {
+#pragma unroll
+            for (int i = 0; i < NW; ++i) w[i] |= s_w[i * kLBlock + tid + 64 * o];
+        }
     }
     w[kSelf >> 5] &= ~(1u << (kSelf & 31));  // z_j is its own first hit
     int cnt = 0;
@@ -206,7 +235,7 @@ struct MarkCand {
 template <class LT, int R, int FEW, int MANY>
 __global__ __launch_bounds__(kLBlock, 7) void walk_marked_kernel(DeviceBVH bvh, GBufView g, OccView occ, LT L,
                                                                  uint32_t *bits, const uint32_t *lists,
-                                                                 uint32_t per_xcd) {
+                                                                 uint32_t per_xcd, uint32_t few_step) {
     constexpr int D = 2 * R, SIDE = 4 * R + 1, NW = (SIDE * SIDE + 31) / 32;
     constexpr int kSelf = D * SIDE + D;
     constexpr float kInvSide = 1.0f / (float)SIDE;
@@ -228,7 +257,8 @@ __global__ __launch_bounds__(kLBlock, 7) void walk_marked_kernel(DeviceBVH bvh, 
         nmany += lists[x * kCountStride + 1];
     }
     const uint32_t per_many = min(max(nmany / kManyStep, 2u), (uint32_t)MANY);
-    const uint32_t few_runs = (nfew + FEW - 1) / FEW, many_runs = (nmany + per_many - 1) / per_many;
+    const uint32_t per_few = min(max(nfew / few_step, 1u), (uint32_t)FEW);
+    const uint32_t few_runs = (nfew + per_few - 1) / per_few, many_runs = (nmany + per_many - 1) / per_many;
     const uint32_t xcd = blockIdx.x & 7;
     const uint32_t stride = (gridDim.x / 8) * (kLBlock / 64);
     const int b = lane / NW, wi = lane - b * NW;  // this lane's word of the run
@@ -247,7 +277,7 @@ __global__ __launch_bounds__(kLBlock, 7) void walk_marked_kernel(DeviceBVH bvh, 
             }
             continue;
         }
-        const uint32_t per = many ? per_many : (uint32_t)FEW, all = many ? nmany : nfew;
+        const uint32_t per = many ? per_many : per_few, all = many ? nmany : nfew;
         const uint32_t c0 = ri * per;
         const int nrun = (int)min(per, all - c0);
         uint32_t j = 0;
@@ -342,6 +372,7 @@ static hipError_t launch_t(const DeviceBVH &bvh, const GBufView &g, const OccVie
     const int per = (nt + 7) / 8;
     const dim3 grid(8 * ((per + kLTileRun - 1) / kLTileRun) * kLTileRun), block(kLBlock);
     const size_t lds = (size_t)nl * 3 * sizeof(float) * light_cells(radius);
+    const uint32_t few_step = bvh.ntris >= kSmallMesh ? kFewStep : kFewStepSmall;
     // (no more than the frame's pixels could fill)
     const int blocks = min(12288, 8 * (per + 1));
 #define OCR_VL(R_, FEW_, MANY_)                                                                                       \
@@ -349,7 +380,7 @@ static hipError_t launch_t(const DeviceBVH &bvh, const GBufView &g, const OccVie
         hipLaunchKernelGGL((mark_pairs_kernel<LT, R_>), grid, block, lds, st, g, occ, L, bits, lists, per_xcd,     \
                            tiles_x, nt);                                                                          \
         hipLaunchKernelGGL((walk_marked_kernel<LT, R_, FEW_, MANY_>), dim3(blocks), block, 0, st, bvh, g, occ, L, bits,    \
-                           lists, per_xcd);                                                                       \
+                           lists, per_xcd, few_step);                                                                       \
     } while (0)
     // (runs of 6 of few marks: 8 measured 2% faster at 1080p and 6% slower at 720p)
     if (radius == 1) OCR_VL(1, 6, 6);
