@@ -31,6 +31,9 @@ __device__ inline const LightF &light_at(const LightSetF &S, int l) { return S.l
 // first and in shorter runs: their runs take up to 20 walks, and one that starts
 // late is the launch's end (1080p window 3 by one list and runs of 8: 0.47 ms).
 constexpr int kFewMarks = 8;
+// Most candidates of a run (8 of few marks measured 2% faster at 1080p and 6%
+// slower at 720p).
+constexpr int kMarkRun = 6;
 // Candidates of many marks per further one in a run (2 to 6): a run's walks are
 // fuller with more, once every wave has several runs (1920x1080 boxes window 3,
 // 119000 candidates, runs of 1 / 2 / 4: 0.230 / 0.185 / 0.176 ms; 1280x720 terrain
@@ -227,25 +230,24 @@ struct MarkCand {
     uint32_t hj;
 };
 
-// The walks of the marked pairs: a wave takes a run of RUN listed candidates,
+// The walks of the marked pairs: a wave takes a run of listed candidates,
 // lists their marks (lane = word), and each 64 of them take a lane each: the
 // density decides whether the pair is one, and a shared any-hit walk of the
 // segments its bit.  Bounded to 7 waves per SIMD (a few words spill; 6 and 8
 // measured up to 3% slower).
-template <class LT, int R, int FEW, int MANY>
+template <class LT, int R>
 __global__ __launch_bounds__(kLBlock, 7) void walk_marked_kernel(DeviceBVH bvh, GBufView g, OccView occ, LT L,
                                                                  uint32_t *bits, const uint32_t *lists,
                                                                  uint32_t per_xcd, uint32_t few_step) {
     constexpr int D = 2 * R, SIDE = 4 * R + 1, NW = (SIDE * SIDE + 31) / 32;
     constexpr int kSelf = D * SIDE + D;
     constexpr float kInvSide = 1.0f / (float)SIDE;
-    constexpr int RUN = FEW > MANY ? FEW : MANY;
-    static_assert(RUN * NW <= 64, "a lane per word");
-    constexpr int kPairs = FEW * kFewMarks > MANY * SIDE * SIDE ? FEW * kFewMarks : MANY * SIDE * SIDE;
+    static_assert(kMarkRun * NW <= 64, "a lane per word");
+    constexpr int kPairs = kMarkRun * SIDE * SIDE;
     __shared__ uint32_t s_stack[kLBlock / 64][kStackTotal];
     __shared__ uint16_t s_pair[kLBlock / 64][kPairs];
-    __shared__ uint32_t s_bits[kLBlock / 64][RUN * NW];
-    __shared__ MarkCand s_cand[kLBlock / 64][RUN];
+    __shared__ uint32_t s_bits[kLBlock / 64][kMarkRun * NW];
+    __shared__ MarkCand s_cand[kLBlock / 64][kMarkRun];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     uint16_t *pairs = s_pair[wave];
     uint32_t *out = s_bits[wave];
@@ -256,8 +258,8 @@ __global__ __launch_bounds__(kLBlock, 7) void walk_marked_kernel(DeviceBVH bvh, 
         nfew += lists[x * kCountStride];
         nmany += lists[x * kCountStride + 1];
     }
-    const uint32_t per_many = min(max(nmany / kManyStep, 2u), (uint32_t)MANY);
-    const uint32_t per_few = min(max(nfew / few_step, 1u), (uint32_t)FEW);
+    const uint32_t per_many = min(max(nmany / kManyStep, 2u), (uint32_t)kMarkRun);
+    const uint32_t per_few = min(max(nfew / few_step, 1u), (uint32_t)kMarkRun);
     const uint32_t few_runs = (nfew + per_few - 1) / per_few, many_runs = (nmany + per_many - 1) / per_many;
     const uint32_t xcd = blockIdx.x & 7;
     const uint32_t stride = (gridDim.x / 8) * (kLBlock / 64);
@@ -375,17 +377,16 @@ static hipError_t launch_t(const DeviceBVH &bvh, const GBufView &g, const OccVie
     const uint32_t few_step = bvh.ntris >= kSmallMesh ? kFewStep : kFewStepSmall;
     // (no more than the frame's pixels could fill)
     const int blocks = min(12288, 8 * (per + 1));
-#define OCR_VL(R_, FEW_, MANY_)                                                                                       \
+#define OCR_VL(R_)                                                                                       \
     do {                                                                                                          \
         hipLaunchKernelGGL((mark_pairs_kernel<LT, R_>), grid, block, lds, st, g, occ, L, bits, lists, per_xcd,     \
                            tiles_x, nt);                                                                          \
-        hipLaunchKernelGGL((walk_marked_kernel<LT, R_, FEW_, MANY_>), dim3(blocks), block, 0, st, bvh, g, occ, L, bits,    \
+        hipLaunchKernelGGL((walk_marked_kernel<LT, R_>), dim3(blocks), block, 0, st, bvh, g, occ, L, bits,    \
                            lists, per_xcd, few_step);                                                                       \
     } while (0)
-    // (runs of 6 of few marks: 8 measured 2% faster at 1080p and 6% slower at 720p)
-    if (radius == 1) OCR_VL(1, 6, 6);
-    else if (radius == 2) OCR_VL(2, 6, 6);
-    else OCR_VL(3, 6, 6);
+    if (radius == 1) OCR_VL(1);
+    else if (radius == 2) OCR_VL(2);
+    else OCR_VL(3);
 #undef OCR_VL
     return hipGetLastError();
 }
