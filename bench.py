@@ -69,6 +69,15 @@ def alu_roof(tops, **extra):
              frac_unpacked=round(tops / VALU_PEAK_TOPS, 4))
     d.update(extra)
     return d
+
+
+def equivalent(roof, of):
+    """The entry of a kernel that leaves out work which `achieved` counts: the rate
+    at which it does the work of `of`, and no fraction of a peak."""
+    roof.update(peak=None, frac=None, peak_unpacked=None, frac_unpacked=None, equivalent_of=of)
+    return roof
+
+
 # FP32 operations of one test of one ray or segment, counted from the kernels
 # (the counted tests are those each ray or segment needs on its own; lanes
 # of a wave that execute a test their segment does not need are not useful
@@ -110,6 +119,21 @@ def window_reuse_ops(r, mode, bilinear=False):
         g += side * side * OPS_BILIN_DENS + tw * tw * OPS_BILIN_G
     return side * side * OPS_DENS[mode] + side * tw * 2 * r + tw * tw * 2 * r + tw * tw * 2 + g
 
+
+
+def window_kernel(mode, unbiased, bilinear, r):
+    """The window reuse kernel of a 1080p frame (256 lanes; 0 for the radii that
+    share a kernel)."""
+    lt = "ocr::LightSetF" if mode == "shadow2" else "ocr::LightBilinF" if bilinear else "ocr::LightF"
+    m = {"ao": 0, "shadow": 1, "shadow_sa": 2, "di": 3, "shadow2": 1}[mode]
+    return f"ocr::reuse_window_kernel<{m}, {'true' if unbiased else 'false'}, {lt}, {r if 1 <= r <= 3 else 0}, 256>"
+
+
+def pair_body(mode, unbiased, r):
+    """Whether that kernel forms only the densities of marked pairs."""
+    return mode != "ao" and (1 if unbiased else 2) <= r <= 3 and (unbiased or mode != "shadow2")
+
+
 WORKLOADS = {
     "ao_1080p": dict(mode="ao", width=1920, height=1080, radius=2.0, window_r=3, scene_seed=2, sample_seed=1),
     "shadow_1080p": dict(mode="shadow", width=1920, height=1080, radius=2.0, window_r=3, scene_seed=2,
@@ -138,8 +162,8 @@ SERVED_SCENES = [dict(seed=100 + i, cells=c, spheres=n)
 SERVED_SIZES = [(1280, 720), (1920, 1080), (2560, 1440)]
 
 
-TRACE_TU = ["density.hpp", "lights.hpp", "ocr_common.hpp", "shaft.hip", "trace.hip", "trace_pixel.hpp", "traverse.hpp",
-            "validate.hpp"]
+TRACE_TU = ["density.hpp", "lights.hpp", "ocr_common.hpp", "shaft.hip", "shaft_box.hpp", "trace.hip",
+            "trace_pixel.hpp", "traverse.hpp", "validate.hpp"]
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "ao_1080p_hbm_traffic.md")
 
 
@@ -464,14 +488,15 @@ def run_frame(args, workload=None, ctx=None, cpu_seconds=None, amortised_reps=0)
     val_tops = val_ops / (per["validate"] * 1e-3) / 1e12
     reuse_tops = hits * window_reuse_ops(r, mode, bilinear) / (per["reuse_biased"] * 1e-3) / 1e12
     if dominant == "validate":
-        # traversal and densities are VALU-bound: price the useful operations of
-        # the counted walk (AO windows decide most pairs on the matrix cores
-        # instead, the light effects leave out most densities)
-        # one validation per light type (single-light kernels carry LightF)
+        # the useful operations of the counting walk.  These frames' kernels leave
+        # much of them out (AO windows decide most pairs on the matrix cores, the
+        # light effects form few of the densities), so the rate is the walk's
+        # equivalent; `validate` also holds the launches that list the candidates.
+        # One validation per light type (single-light kernels carry LightF).
         lt = "ocr::LightSetF" if mode == "shadow2" else "ocr::LightF"
-        kname = "ocr::validate_shaft_kernel" if mode == "ao" else f"ocr::walk_marked_kernel<{lt}, {r}, 6, 6>"
+        kname = "ocr::validate_shaft_kernel" if mode == "ao" else f"ocr::walk_marked_kernel<{lt}, {r}>"
         traffic = measured_traffic(kname) if workload == "ao_1080p" else None
-        roof = alu_roof(val_tops, traffic=traffic, kernel=kname)
+        roof = equivalent(alu_roof(val_tops, traffic=traffic, kernel=kname), "the counting walk")
     elif dominant in ("reuse_biased", "reuse_unbiased"):
         # a 7x7 window reuse binds on the VALU (up to 169 densities per
         # candidate): its useful operations against the VALU peak, with its
@@ -481,13 +506,20 @@ def run_frame(args, workload=None, ctx=None, cpu_seconds=None, amortised_reps=0)
         # (the unbiased launch also reads each pixel's validation words)
         vbytes = (((4 * r + 1) ** 2 + 31) // 32) * 4 * W * H if dominant == "reuse_unbiased" else 0
         gbs = (reuse_bytes + vbytes) / (t_ms * 1e-3) / 1e9
-        lt = "ocr::LightSetF" if mode == "shadow2" else "ocr::LightBilinF" if bilinear else "ocr::LightF"
-        kname = (f"ocr::reuse_window_kernel<{ {'ao': 0, 'shadow': 1, 'shadow_sa': 2, 'di': 3, 'shadow2': 1}[mode]}, "
-                 f"{'true' if dominant == 'reuse_unbiased' else 'false'}, {lt}>")
-        roof = alu_roof(tops, traffic=None, kernel=kname, hbm_gbs=round(gbs, 1), hbm_frac=round(gbs / HBM_PEAK_GBS, 4))
+        unbiased = dominant == "reuse_unbiased"
+        roof = alu_roof(tops, traffic=None, kernel=window_kernel(mode, unbiased, bilinear, r), hbm_gbs=round(gbs, 1),
+                        hbm_frac=round(gbs / HBM_PEAK_GBS, 4))
+        if pair_body(mode, unbiased, r):
+            equivalent(roof, "every density")
     else:
         roof = dict(bound="hbm", achieved=round(reuse_gbs, 2), peak=HBM_PEAK_GBS, unit="GB/s",
                     frac=round(reuse_gbs / HBM_PEAK_GBS, 5), traffic=None, kernel=dominant)
+
+    reuse_roof = alu_roof(reuse_tops, hbm_gbs=round(reuse_gbs, 1), hbm_frac=round(reuse_gbs / HBM_PEAK_GBS, 4),
+                          kernel=window_kernel(mode, False, bilinear, r),
+                          ops_per_candidate=window_reuse_ops(r, mode, bilinear))
+    if pair_body(mode, False, r):
+        equivalent(reuse_roof, "every density")
 
     result = {
         "metric": "Mrays/s + reuse-pass GB/s at 1080p; frames/s and p99 frame latency served",
@@ -517,10 +549,7 @@ def run_frame(args, workload=None, ctx=None, cpu_seconds=None, amortised_reps=0)
         "reused_samples_per_s": round(hits * (2 * r + 1) ** 2 / (per["reuse_biased"] * 1e-3), 1),
         "pair_densities_per_s": round(pair_evals / (per["reuse_biased"] * 1e-3), 1),
         "biased_frame_ms": round(per["trace"] + per["reuse_biased"], 4),
-        "reuse_roofline": alu_roof(reuse_tops, hbm_gbs=round(reuse_gbs, 1), hbm_frac=round(reuse_gbs / HBM_PEAK_GBS, 4),
-                               kernel=f"ocr::reuse_window_kernel<{ {'ao': 0, 'shadow': 1, 'shadow_sa': 2, 'di': 3, 'shadow2': 1}[mode]}, false, "
-                                      f"{'ocr::LightSetF' if mode == 'shadow2' else 'ocr::LightBilinF' if bilinear else 'ocr::LightF'}>",
-                               ops_per_candidate=window_reuse_ops(r, mode, bilinear)),
+        "reuse_roofline": reuse_roof,
         "rays_per_step": rays,
         "negative_pixel_fraction": negative,
         "occluder_hits": hits,
