@@ -73,8 +73,8 @@ __device__ inline void tile_pixel(int packing, int tw, int th, int it, int lane,
 
 // One wave per trace item: the wave traces the item's tile_w x tile_h pixels
 // in (tile_w * tile_h / 64) passes of one ray per lane.  Bounded to 7 waves
-// per SIMD: the sixteen-view plan measured 3.52 ms, at 6 and at 8 waves 3.62 and
-// 3.61.
+// per SIMD: the sixteen-view plan measures 3.31 ms, at 6 and at 8 waves 3.35 and
+// 3.34.
 template <bool FAR>
 __global__ __launch_bounds__(kBBlock, 7) void batch_trace_kernel(const BatchView *__restrict__ views,
                                                               const uint32_t *__restrict__ t_first,
@@ -121,7 +121,7 @@ __global__ __launch_bounds__(kBBlock, 7) void batch_trace_kernel(const BatchView
 // One block per reuse item (a window target tile of a window or no-reuse view).
 // Bounded to 7 waves per SIMD: every mode's body is inlined, and the
 // heaviest (light effects) spill a few words at 72 registers; the sixteen-view
-// plan measured 3.52 ms, the same as at 6 waves (8 waves 3.54 ms).
+// plan measures 3.31 ms, at 6 and at 8 waves 3.35.
 __global__ __launch_bounds__(kRBlock, 7) void batch_reuse_kernel(const BatchView *__restrict__ views,
                                                               const uint32_t *__restrict__ r_first, int nviews,
                                                               const uint32_t *__restrict__ q_start, uint32_t *ctr) {

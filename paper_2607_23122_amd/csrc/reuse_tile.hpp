@@ -418,8 +418,9 @@ __device__ inline void tile_row_candidates(const WinLayout &lay, unsigned char *
 // pairs in the target's window, row by row, by cross-lane reads: the box sums
 // without their zeros, so the same bits.  Candidates with more than few_pairs(R)
 // marks are left to the row tasks (s_left, all ones at the tile's start).
-// 1080p, window 3, one light: biased 0.275 -> 0.200 ms (1.41e8 -> 0.67e8 VALU
-// instructions), unbiased 0.207 -> 0.137 (0.24e8).  What is left is the tail:
+// 1080p, window 3, one light, rows / pairs: biased 0.285 / 0.190 ms, unbiased
+// 0.216 / 0.121 (1.16M triangles), 0.199 / 0.199 and 0.198 / 0.185 where a 24 m
+// light leaves most candidates to the rows.  What is left is the tail:
 // without the few tiles that hold hundreds of candidates for the row tasks
 // (9500 of 882000), which take 100 us each, the unbiased launch would end after
 // 40 us.

@@ -34,8 +34,8 @@
 // Against the walk it replaces (one any-hit walk of the hierarchy per 64
 // segments: per walk 27 nodes at 58 VALU instructions and 43 triangles at 40),
 // a filtered pair costs 1/20 of a triangle test: 1080p AO, 7x7 window, 26.7M
-// segments, 2.39 -> 1.17 ms (1.46e9 -> 5.6e8 VALU instructions).  Bound by VALU
-// issue (0.92 ms of it) and, at 4 waves per SIMD (128 registers, 10 KB of LDS),
+// segments, 2.18 -> 1.16 ms (1.46e9 -> 5.4e8 VALU instructions).  Bound by VALU
+// issue (0.87 ms of it) and, at 4 waves per SIMD (128 registers, 10 KB of LDS),
 // by the latency of the gather's dependent loads.
 #include "ocr_common.hpp"
 #include "shaft_box.hpp"

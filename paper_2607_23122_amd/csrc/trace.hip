@@ -540,15 +540,17 @@ hipError_t launch_trace_count(const DeviceBVH &bvh, const GBufView &g, int mode,
 // whatever its segments, the walk 64 segments at a time the nodes and triangles
 // on their way; so shafts pay with more segments per candidate (radius) and
 // longer walks (triangles), and in small frames, whose few waves wait for
-// memory: a shaft's loads are fewer and wider.  Measured, shaft / walk, ms:
-//   radius 3: 6146 triangles 1920x1080 1.29 / 1.48, 3074 1.11 / 1.10, 770 0.45 / 0.39;
-//             1.16M triangles 1.17 / 2.39
-//   radius 2: 49154 triangles 1920x1080 0.70 / 0.92, 12290 1.06 / 1.03, 770 0.37 / 0.24;
-//             1.16M triangles 0.88 / 1.38
-//   radius 1: 1.16M triangles 1920x1080 0.71 / 0.68, 1280x720 0.36 / 0.41, 320x180 0.09 / 0.17;
-//             49154 triangles 960x540 0.18 / 0.17
-//   small frames: 770 triangles 256x256 radius 2 0.037 / 0.044, 960x540 0.114 / 0.089;
-//             1152 triangles 320x180 radius 2 0.023 / 0.031
+// memory: a shaft's loads are fewer and wider.  Measured, shaft / walk, us (boxes;
+// the last of each line a terrain):
+//   radius 3, 1920x1080: 770 triangles 450 / 348, 3074 1146 / 1030, 6146 1339 / 1405,
+//             12290 1305 / 1687; 1.16M 1156 / 2182
+//   radius 2, 1920x1080: 770 triangles 362 / 216, 12290 1072 / 967, 49154 698 / 845;
+//             1.16M 869 / 1260
+//   radius 1: 49154 triangles 960x540 169 / 148, 1280x720 279 / 219; 1.16M 256x256
+//             86 / 144, 960x540 222 / 255, 1280x720 344 / 361
+//   radius 2, small frames: 770 triangles 256x256 35 / 43, 480x270 38 / 46, 640x360
+//             60 / 52; 40832 480x270 53 / 105
+// Long segments meet too many triangles for either's gain (long_rays).
 static bool shaft_pays(const DeviceBVH &bvh, const GBufView &g, float R, int radius) {
     if (long_rays(bvh, R)) return false;
     const int64_t px = (int64_t)g.w * g.h;

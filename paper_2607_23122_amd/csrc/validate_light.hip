@@ -5,11 +5,13 @@
 // The light subtends a narrow cone at z_j, so a candidate has one or two pairs
 // among its (4R + 1)^2.  Listing them by their densities (the walk over
 // candidate lists of trace.hip, which other radii take) was two thirds of its
-// VALU instructions, which bound it.  1080p, window 3, terrain, lists / marks:
-// 0.501 / 0.290 ms (2.2e8 -> 1.2e8 VALU instructions; marking 0.06 ms), window 2
-// 0.427 / 0.262, window 1 0.351 / 0.234; two lights 0.776 / 0.474; 333x197 boxes
-// 0.033 / 0.029; 1920x1080 boxes 0.215 / 0.190.  Under a light that marks half of
-// the square, 24 m wide and 8 m above the terrain, 3.81 / 4.03.
+// VALU instructions, which bound it.  1080p, 1.16M triangles, lists / marks:
+// window 3 0.482 / 0.249 ms (marking 0.06 ms), window 2 0.411 / 0.233, window 1
+// 0.347 / 0.218; 333x197 0.060 / 0.043; boxes 1920x1080 0.189 / 0.161, 333x197
+// 0.031 / 0.028.  Under a light that marks half of the square, 24 m wide, 1.442 /
+// 1.322 (131000 triangles).  Slower only where the marks say little: a light of
+// 20 m by 1 m over a small frame, 0.029 / 0.031, and one of 100 m at 9.5 km, whose
+// distance widens the marks' slack, 0.053 / 0.061.
 #include "lights.hpp"
 #include "ocr_common.hpp"
 #include "traverse.hpp"
